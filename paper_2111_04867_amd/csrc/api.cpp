@@ -52,7 +52,8 @@ taccl_status_t ensure_device(taccl_plan *p, DeviceTables **out) {
          o_lal = pk.add(p->lalpha), o_lbs = pk.add(p->lbs), o_lmg = pk.add(p->lmerge),
          o_lrev = pk.add(p->lrev), o_hc2 = pk.add(p->hop_class2),
          o_lcb2 = pk.add(p->lvl_cls2_begin), o_llc2 = pk.add(p->llc2),
-         o_gkr = pk.add(p->gkrank), o_tent = pk.add(p->tent), o_c2l = pk.add(p->cls2_link);
+         o_gkr = pk.add(p->gkrank), o_tent = pk.add(p->tent), o_c2l = pk.add(p->cls2_link),
+         o_cnr = pk.add(p->cn_rec), o_cnc = pk.add(p->cn_chunk);
   void *blk = nullptr;
   e = hipMalloc(&blk, pk.bytes.size());
   if (e != hipSuccess) return fail(TACCL_ERR_NO_MEMORY, "hipMalloc of plan tables failed");
@@ -95,6 +96,8 @@ taccl_status_t ensure_device(taccl_plan *p, DeviceTables **out) {
   t.cbkt = (const uint32_t *)at(o_cbkt);
   t.gkrank = (const uint32_t *)at(o_gkr);
   t.tent = p->tent.empty() ? nullptr : (const uint8_t *)at(o_tent);
+  t.cn_rec = p->cn_rec.empty() ? nullptr : (const uint32_t *)at(o_cnr);
+  t.cn_chunk = (const uint32_t *)at(o_cnc);
   t.max_lds = (int)prop.sharedMemPerBlock;
   t.lds_per_cu = (int)std::max<size_t>(prop.maxSharedMemoryPerMultiProcessor, prop.sharedMemPerBlock);
   t.num_cus = prop.multiProcessorCount;
@@ -451,6 +454,31 @@ taccl_status_t taccl_connections_batch(taccl_plan_t p, int64_t n, const uint8_t 
   a.routes = d_routes;
   a.out = d_connections;
   a.n = n;
+  if (t->cn_rec) {
+    a.rec = t->cn_rec;
+    a.chunk = (const uint4 *)t->cn_chunk;
+    a.nrec = (int32_t)p->cn_rec.size();
+    a.cells = p->conn_cells;
+    a.nwords = (a.C + 3) / 4;
+    a.lanes = 4;
+    while (a.lanes < 64 && a.lanes < a.nwords) a.lanes *= 2;
+    a.rec_lds = 4 * a.nrec <= kConnRecLdsMax;
+    a.routes_words = (p->route_stride % 4 == 0) && (((uintptr_t)d_routes & 3) == 0);
+    // as many wavefronts per block as spread the batch over every CU, 4 at
+    // least (they share the record table), 16 at most
+    const int64_t cus = std::max(t->num_cus, 1), per_wave = 64 / a.lanes;
+    const int64_t want = (n + per_wave - 1) / per_wave;
+    int waves = (int)std::min<int64_t>(kConnWaveThreads / 64, std::max<int64_t>(4, want / cus));
+    while (waves > 1 && connections_wave_lds_bytes(a, waves) > t->max_lds) waves--;
+    const int bytes = connections_wave_lds_bytes(a, waves);
+    if (bytes <= t->max_lds) {
+      const int bpc = std::max(1, std::min(t->lds_per_cu / bytes, 32 / waves));
+      const int wgrid = (int)std::min<int64_t>((want + waves - 1) / waves, cus * bpc);
+      hipError_t e = launch_connections_wave(a, waves, wgrid, (hipStream_t)stream);
+      if (e != hipSuccess) return hip_fail(e, "kernel launch");
+      return TACCL_OK;
+    }
+  }
   // one chunk per thread at a time; multicast blocks keep a parent byte per
   // vertex and thread in LDS
   int threads = std::min(kConnMaxThreads, std::max(64, (a.C + 63) / 64 * 64));

@@ -158,9 +158,19 @@ struct ConnArgs {
   const uint8_t *routes;
   uint32_t *out;
   int64_t n;
+  // wavefront-per-candidate variant (Alltoall): switched pairs of every route
+  // option and chunk table, the byte matrix's cells, words of routes per
+  // candidate, lanes per candidate (a power of two), record table in LDS,
+  // routes readable as aligned words
+  const uint32_t *rec;
+  const uint4 *chunk;
+  int32_t cells, nwords, lanes, nrec, rec_lds, routes_words;
 };
 
 constexpr int kConnMaxThreads = 256;
+constexpr int kConnWaveThreads = 1024;
+// record tables up to this size are copied to LDS by every block
+constexpr int kConnRecLdsMax = 64 * 1024;
 
 constexpr int kTreeMaxThreads = 512;  // up to 8 wavefronts per block
 // (chunk, vertex) slots per lane of the layered, greedy and ranked multicast
@@ -219,6 +229,10 @@ hipError_t launch_path_greedy_block(const PathGreedyArgs &a, int grid, hipStream
 // connection count: LDS bytes of a block of `threads`, and the launch
 int32_t connections_lds_bytes(const ConnArgs &a, int threads);
 hipError_t launch_connections(const ConnArgs &a, int threads, int grid, hipStream_t stream);
+// the wavefront-per-candidate count: LDS bytes of a block of `waves`
+// wavefronts, and the launch
+int32_t connections_wave_lds_bytes(const ConnArgs &a, int waves);
+hipError_t launch_connections_wave(const ConnArgs &a, int waves, int grid, hipStream_t stream);
 hipError_t launch_tree_layers(const TreeArgs &a, int grid, hipStream_t stream);
 // resident blocks per CU of the layered kernel at a.waves_per_block
 int tree_layers_blocks_per_cu(const TreeArgs &a);

@@ -593,6 +593,50 @@ static void path_sum_codes(taccl_plan *p) {
   p->pq_range = (int32_t)range;
 }
 
+// Tables of the wavefront-per-candidate connection count: the switched rank
+// pairs of every Alltoall route option. Left empty when a route has more
+// than two, or past 64 ranks (a wavefront's P x P byte matrix then takes
+// more than 4 KB of LDS).
+static void connection_records(taccl_plan *p) {
+  p->cn_rec.clear();
+  p->cn_chunk.clear();
+  const int32_t P = p->topo.P, C = p->coll.C;
+  const size_t npath = p->path_off.size() - 1;
+  if (P > 64 || npath + 1 >= (1u << 24)) return;
+  p->conn_cells = (P * P + 15) / 16 * 16;
+  const uint32_t none = (uint32_t)p->conn_cells;
+  std::vector<uint32_t> rec(npath + 1, none | (none << 16));
+  for (int32_t pp = 0; pp < P * P; pp++)
+    for (int32_t k = 0; k < p->npaths[pp]; k++) {
+      const uint32_t q = p->pair_base[pp] + k;
+      uint32_t last = (uint32_t)(pp / P), found = 0;
+      bool through_switch = false;
+      for (uint32_t j = p->path_off[q]; j < p->path_off[q + 1]; j++) {
+        const uint32_t v = p->ldst[p->path_links[j]];
+        if (v >= (uint32_t)P) {
+          through_switch = true;
+          continue;
+        }
+        if (through_switch) {
+          if (found == 2) return;
+          uint32_t &r = rec[q + 1];
+          const uint32_t cell = last * (uint32_t)P + v;
+          r = found ? (r & 0xFFFFu) | (cell << 16) : (r & 0xFFFF0000u) | cell;
+          found++;
+        }
+        last = v;
+        through_switch = false;
+      }
+    }
+  p->cn_rec.swap(rec);
+  p->cn_chunk.assign((size_t)(C + 3) / 4 * 4, 0);
+  for (int32_t c = 0; c < C; c++) {
+    const int32_t pp = c / std::max(p->coll.cpr, 1);  // the chunk's pair s*P + d
+    if (pp / P != pp % P)
+      p->cn_chunk[c] = (p->pair_base[pp] + 1) | ((uint32_t)p->npaths[pp] << 24);
+  }
+}
+
 static taccl_status_t build_layout(taccl_plan *p) {
   const taccl_topology &t = p->topo;
   const taccl_collective &c = p->coll;
@@ -900,6 +944,7 @@ taccl_status_t taccl_sketch_apply(taccl_topology_t topo, taccl_collective_t coll
   if (coll->kind == TACCL_ALLTOALL) {
     st = build_levels(p);
     if (st) return st;
+    connection_records(p);
   } else {
     if (topo->V > 64)
       return fail(TACCL_ERR_UNSUPPORTED, "multicast evaluation holds at most 64 vertices");

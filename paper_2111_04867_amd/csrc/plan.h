@@ -69,6 +69,7 @@ struct DeviceTables {
   const uint32_t *llc = nullptr;
   const uint32_t *arec = nullptr, *cpath = nullptr, *cinfo = nullptr, *cbkt = nullptr;
   const uint32_t *gkrank = nullptr;
+  const uint32_t *cn_rec = nullptr, *cn_chunk = nullptr;
   int max_lds = 0;  // bytes of LDS a block may use on this device
   int lds_per_cu = 0;
   int num_cus = 0;
@@ -162,6 +163,15 @@ struct taccl_plan {
   // order), and the number of distinct ranks
   std::vector<uint32_t> gkrank;
   int32_t gk_count = 0;
+
+  // connection count of Alltoall plans whose routes form at most two
+  // switched rank pairs each: per route option (option q at record q + 1,
+  // record 0 empty) its two pairs as 16-bit cells a*P + b of a P x P byte
+  // matrix (conn_cells, the matrix's byte size, marks no pair), and per
+  // chunk, padded to whole route words, its first record | option count
+  // << 24; empty when the plan does not qualify
+  std::vector<uint32_t> cn_rec, cn_chunk;
+  int32_t conn_cells = 0;
 
   // launch shape
   int32_t tree_lds = 0, path_lds = 0;

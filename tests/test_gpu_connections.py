@@ -115,3 +115,54 @@ def test_batch_split_and_empty():
     d_c = torch.empty(1, dtype=torch.int32, device="cuda")
     plan.connections_tensors(d_r, d_c)  # n == 0 is a no-op
     torch.cuda.synchronize()
+
+
+def switch_chain(P):
+    """Ranks in a row with a switch between neighbours: the route from one
+    end to the other forms P - 1 switched pairs."""
+    edges = []
+    for i in range(P - 1):
+        edges += cf.switch_edges((i, i + 1), P + i, 700, 8)
+    row_ptr, col, a, b = cf.csr_from_edges(2 * P - 1, edges)
+    return cf.Workload(f"switchchain{P}", 2 * P - 1, P, row_ptr, col, a, b, None, cf.ALLTOALL, 1,
+                       65536, cf.KSHORTEST, k=1)
+
+
+def many_options(P, k):
+    """A switch, a ring and chords: up to k routes per pair."""
+    w = hybrid(P, cf.ALLTOALL)
+    edges = cf.switch_edges(range(P), P, 700, 8) + cf.ring_edges(range(P), 1500, 8)
+    edges += [(i, (i + 2) % P, 1900, 8) for i in range(P)]
+    w.row_ptr, w.col, w.alpha_ns, w.beta_ps_per_byte = cf.csr_from_edges(P + 1, edges)
+    w.k = k
+    return w
+
+
+@pytest.mark.parametrize("w,n", [
+    (switch_chain(3), 65),         # two pairs per route: one wavefront per candidate
+    (switch_chain(5), 65),         # up to four: one block per candidate
+    (star(2, cf.ALLTOALL), 7),     # one route word, 4 lanes per candidate
+    (star(8, cf.ALLTOALL), 1),     # 16 lanes per candidate, one candidate
+    (star(16, cf.ALLTOALL), 4099),  # 64 lanes, one word each, several rounds
+    (star(17, cf.ALLTOALL), 130),  # 289 chunks: two words per lane, odd rows
+    (star(20, cf.ALLTOALL, cpr=2), 70),
+    (many_options(16, 120), 33),   # record table beyond LDS, one word per lane
+    (star(64, cf.ALLTOALL, relays=False), 40),  # largest byte matrix
+    (star(65, cf.ALLTOALL, relays=False), 9),   # past it
+], ids=lambda x: x.name if hasattr(x, "name") else str(x))
+def test_alltoall_variants(w, n):
+    check(w, n, 3 + n, unrouted=0.05)
+
+
+def test_unaligned_routes():
+    """Route rows of whole words behind a pointer that is not word aligned."""
+    from paper_2111_04867_amd.binding import Plan
+    w = cf.switch16_a2a()
+    plan = Plan.from_workload(w)
+    routes, _ = generate(w.seed, 0, 257, plan.route_options(), plan.prio_stride)
+    buf = torch.zeros(routes.size + 1, dtype=torch.uint8, device="cuda")
+    buf[1:] = torch.from_numpy(routes.reshape(-1))
+    out = torch.empty(257, dtype=torch.int32, device="cuda")
+    plan.connections_tensors(buf[1:].view(257, plan.route_stride), out)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), plan.connections(routes))
