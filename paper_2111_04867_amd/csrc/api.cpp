@@ -52,7 +52,7 @@ taccl_status_t ensure_device(taccl_plan *p, DeviceTables **out) {
          o_lal = pk.add(p->lalpha), o_lbs = pk.add(p->lbs), o_lmg = pk.add(p->lmerge),
          o_lrev = pk.add(p->lrev), o_hc2 = pk.add(p->hop_class2),
          o_lcb2 = pk.add(p->lvl_cls2_begin), o_llc2 = pk.add(p->llc2),
-         o_gkr = pk.add(p->gkrank), o_tent = pk.add(p->tent), o_c2l = pk.add(p->cls2_link),
+         o_gkr = pk.add(p->gkrank), o_rimg = pk.add(p->rank_img), o_c2l = pk.add(p->cls2_link),
          o_cnr = pk.add(p->cn_rec), o_cnc = pk.add(p->cn_chunk);
   void *blk = nullptr;
   e = hipMalloc(&blk, pk.bytes.size());
@@ -95,7 +95,7 @@ taccl_status_t ensure_device(taccl_plan *p, DeviceTables **out) {
   t.cinfo = (const uint32_t *)at(o_cinfo);
   t.cbkt = (const uint32_t *)at(o_cbkt);
   t.gkrank = (const uint32_t *)at(o_gkr);
-  t.tent = p->tent.empty() ? nullptr : (const uint8_t *)at(o_tent);
+  t.rank_img = p->rank_img.empty() ? nullptr : at(o_rimg);
   t.cn_rec = p->cn_rec.empty() ? nullptr : (const uint32_t *)at(o_cnr);
   t.cn_chunk = (const uint32_t *)at(o_cnc);
   t.max_lds = (int)prop.sharedMemPerBlock;
@@ -331,9 +331,9 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     // the ReduceScatter (alone or as an Allreduce's first phase) when every
     // route hop has a reverse link of equal cost and there is no contiguity
     TreeArgs ra = a;
-    const bool ranked = !greedy && a.routes_word_aligned && t->tent &&
+    const bool ranked = !greedy && a.routes_word_aligned && t->rank_img &&
                         tree_rank_layout(*p, ra) > 0 && tree_block_bytes(ra, 1) <= t->max_lds;
-    ra.ent = t->tent;
+    ra.rank_img = (const uint4 *)t->rank_img;
     const bool ranked_rs = ranked && tree_rank_reverse_ok(*p);
     auto launch_ranked = [&](TreeArgs &x) {
       int best_w = 1, best_res = 0, best_bpc = 1;

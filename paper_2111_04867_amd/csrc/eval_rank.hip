@@ -41,6 +41,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <vector>
 
 #include "kernels.h"
 #include "wave.h"
@@ -93,10 +94,10 @@ __global__ __launch_bounds__(kRankMaxThreads) void tree_rank_kernel(TreeArgs a) 
   static_assert(!(kC && kR), "contiguous transfers are not combined with ReduceScatter here");
   extern __shared__ __align__(16) unsigned char lds[];
   const int C = a.C, V = a.V, E = a.E, K = a.K;
-  constexpr int P = 4 * PW;
   const int CV = C * V;
 
-  uint32_t *s_cost = (uint32_t *)(lds + a.o_cost);
+  // ReduceScatter: every link's entry holds its reverse's cost
+  const uint32_t *s_cost = (const uint32_t *)(lds + (kR ? a.o_rcost : a.o_cost));
   uint8_t *s_src = lds + a.o_src;
   uint8_t *s_merge = lds + a.o_merge;  // links that carry contiguous transfers
   uint64_t *s_post = (uint64_t *)(lds + a.o_post);
@@ -109,32 +110,6 @@ __global__ __launch_bounds__(kRankMaxThreads) void tree_rank_kernel(TreeArgs a) 
   // 30 | in the postcondition << 31, and option base | route word base << 16
   // | owner << 24
   uint2 *s_slot = (uint2 *)(lds + a.o_slot);
-  const int OS = a.opt_ostride;
-  for (int j = threadIdx.x; j < E; j += blockDim.x) {
-    // ReduceScatter: every link's entry holds its reverse's cost (a tree
-    // link always has a reverse, checked at plan time)
-    s_cost[j] = kR ? a.cost[a.lrev[j] != 0xFFFFu ? a.lrev[j] : j] : a.cost[j];
-    s_src[j] = (uint8_t)a.lsrc[j];
-    if (kC) s_merge[j] = a.lmerge[j];
-  }
-  for (int j = threadIdx.x; j < P * V * PW; j += blockDim.x) {
-    const int w = j % PW, ov = j / PW, o = ov / V, v = ov - o * V;
-    s_opt[o * OS + w * V + v] = ((const uint32_t *)a.topt)[j];
-  }
-  for (int j = threadIdx.x; j < P * V * P * K; j += blockDim.x) s_ent[j] = a.ent[j];
-  for (int j = threadIdx.x; j < C; j += blockDim.x) {
-    s_post[j] = a.post_mask[j];
-  }
-  for (int j = threadIdx.x; j < CV; j += blockDim.x) {
-    const int c = j / V, v = j - c * V, o = a.owner8[c];
-    const uint32_t post = (uint32_t)((a.post_mask[c] >> v) & 1);
-    s_slot[j] = make_uint2((uint32_t)((o * V + v) * P * K) | ((uint32_t)(c * V) << 20) |
-                               ((uint32_t)(v == o) << 30) | (post << 31),
-                           (uint32_t)(o * OS + v) | ((uint32_t)(c * PW) << 16) |
-                               ((uint32_t)o << 24));
-  }
-  __syncthreads();
-
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   unsigned char *wl = lds + a.o_wave + wave * a.wave_bytes;
   // Region A: one-hot routes, distances, ancestors and heights per slot;
@@ -193,8 +168,18 @@ __global__ __launch_bounds__(kRankMaxThreads) void tree_rank_kernel(TreeArgs a) 
   const uint32_t reach31 = lane >= 32 ? (uint32_t)lane - 31 : 0xFFFFu;
   const int R = a.pj_rounds;
 
+  // The first candidate's inputs are on their way while the block copies the
+  // plan's tables (one prebuilt image of the shared LDS, 16 bytes per thread
+  // and step): a batch that gives a wavefront one or two candidates is mostly
+  // this set-up. Assembling the tables here from the plan's own arrays (a
+  // byte at a time, with divisions by V and P, after a chain of dependent
+  // loads) took 13.0 us for 4096 candidates of an 8-rank cube-mesh Allgather; 9.5 us
+  // now.
   load_routes(first, lane);
   load_prio(first, lane);
+  for (int j = threadIdx.x; j < a.o_wave / 16; j += blockDim.x)
+    ((uint4 *)lds)[j] = a.rank_img[j];
+  __syncthreads();
   for (int64_t i = first; i < a.n; i += stride) {
     // The lane index is hidden from the optimiser once per candidate, so
     // per-slot LDS addresses are recomputed where used instead of being
@@ -722,6 +707,9 @@ int32_t tree_rank_layout(const taccl_plan &p, TreeArgs &a) {
     return o;
   };
   a.o_cost = take(4 * E);
+  // costs of the reverse links (ReduceScatter and an Allreduce's first phase)
+  a.o_rcost = p.coll.kind == TACCL_REDUCESCATTER || p.coll.kind == TACCL_ALLREDUCE ? take(4 * E)
+                                                                                  : a.o_cost;
   a.o_src = take(E);
   a.o_merge = take(E);
   a.o_post = take(8 * C);
@@ -767,6 +755,42 @@ int32_t tree_rank_layout(const taccl_plan &p, TreeArgs &a) {
   w = align16(w + 4 * 65);
   a.wave_bytes = w;
   return a.o_wave + a.wave_bytes;
+}
+
+std::vector<uint8_t> tree_rank_image(const taccl_plan &p) {
+  TreeArgs a{};
+  const int32_t bytes = tree_rank_layout(p, a);
+  if (bytes <= 0 || bytes > 160 * 1024) return {};  // no CU holds it
+  const int32_t C = p.coll.C, V = p.topo.V, E = p.topo.E, P = p.topo.P, K = a.K, PW = P / 4;
+  std::vector<uint8_t> img(a.o_wave, 0);
+  uint8_t *b = img.data();
+  uint32_t *cost = (uint32_t *)(b + a.o_cost), *rcost = (uint32_t *)(b + a.o_rcost);
+  for (int32_t l = 0; l < E; l++) {
+    // a tree link always has a reverse where reverse costs are read
+    // (checked at plan time)
+    if (a.o_rcost != a.o_cost) rcost[l] = p.cost[p.lrev[l] != 0xFFFFu ? p.lrev[l] : l];
+    cost[l] = p.cost[l];
+    b[a.o_src + l] = (uint8_t)p.lsrc[l];
+    b[a.o_merge + l] = p.lmerge[l];
+  }
+  uint64_t *post = (uint64_t *)(b + a.o_post);
+  for (int32_t c = 0; c < C; c++) post[c] = p.post_mask[c];
+  uint8_t *opt = b + a.o_opt;  // byte d of word d / 4
+  for (int32_t o = 0; o < P; o++)
+    for (int32_t v = 0; v < V; v++)
+      for (int32_t d = 0; d < P; d++)
+        opt[4 * (o * a.opt_ostride + d / 4 * V + v) + d % 4] = p.topt[((size_t)o * V + v) * P + d];
+  std::copy(p.tent.begin(), p.tent.end(), b + a.o_ent);
+  uint32_t *slot = (uint32_t *)(b + a.o_slot);
+  for (int32_t c = 0; c < C; c++)
+    for (int32_t v = 0; v < V; v++) {
+      const uint32_t o = (uint32_t)p.coll.owner[c], post_v = (uint32_t)((p.post_mask[c] >> v) & 1);
+      uint32_t *s = slot + 2 * (c * V + v);
+      s[0] = (o * V + v) * P * K | ((uint32_t)(c * V) << 20) | ((uint32_t)((uint32_t)v == o) << 30) |
+             (post_v << 31);
+      s[1] = (o * a.opt_ostride + v) | ((uint32_t)(c * PW) << 16) | (o << 24);
+    }
+  return img;
 }
 
 bool tree_rank_reverse_ok(const taccl_plan &p) {

@@ -65,8 +65,8 @@ struct TreeArgs {
   // per-slot heights and the parent send of each bucket-sorted position
   uint64_t qmagic;
   int32_t qrange;
-  const uint8_t *ent;
-  int32_t o_ent, w_h, o_slot, opt_ostride, w_pj;
+  const uint4 *rank_img;  // the block's shared LDS below o_wave, ready to copy
+  int32_t o_rcost, o_ent, w_h, o_slot, opt_ostride, w_pj;
 };
 
 // Alltoall evaluation: one block per candidate, level by level.
@@ -193,6 +193,9 @@ int32_t tree_block_bytes(const TreeArgs &a, int waves);
 // fills the layout and returns the bytes of a one-wavefront block, or 0
 // when the plan does not meet its conditions.
 int32_t tree_rank_layout(const taccl_plan &p, TreeArgs &a);
+// the ranked kernel's shared LDS tables as one image (its first o_wave
+// bytes); empty when the plan does not meet its conditions
+std::vector<uint8_t> tree_rank_image(const taccl_plan &p);
 // the ranked kernel may run the plan's ReduceScatter (reverse links with
 // equal costs, no contiguity)
 bool tree_rank_reverse_ok(const taccl_plan &p);

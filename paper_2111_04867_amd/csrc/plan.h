@@ -56,7 +56,7 @@ struct DeviceTables {
   const uint8_t *owner8 = nullptr;
   const uint8_t *topt = nullptr;
   const uint32_t *tree_rec4 = nullptr;
-  const uint8_t *tent = nullptr;
+  const uint8_t *rank_img = nullptr;
   const uint32_t *lalpha = nullptr;
   const uint64_t *lbs = nullptr;
   const uint8_t *lmerge = nullptr;
@@ -124,6 +124,8 @@ struct taccl_plan {
   // (o, d) enters vertex v (0xFF where it does not pass v); empty unless
   // every link id fits 8 bits
   std::vector<uint8_t> tent;
+  // the ranked kernel's shared LDS tables, as its blocks copy them
+  std::vector<uint8_t> rank_img;
   // Exact order-preserving compression of tree-path lengths: every
   // remaining or travelled length of a multicast send is a sum of at most
   // V - 1 link costs, and x -> (x * pq_magic) >> 32 is strictly increasing
