@@ -105,6 +105,33 @@ taccl_status_t ensure_device(taccl_plan *p, DeviceTables **out) {
   return TACCL_OK;
 }
 
+// The launch shape of one of the plan's kernels on this device: the block
+// size (1 to max_waves wavefronts) with the most resident wavefronts per CU,
+// by LDS, the 32 wavefronts of a CU and the runtime's occupancy query
+// (per_cu(waves); 0 if it fails). bytes(waves): LDS of a block.
+template <class Bytes, class PerCu>
+LaunchShape launch_shape(taccl_plan *p, DeviceTables *t, ShapeOf which, int max_waves, Bytes bytes,
+                         PerCu per_cu) {
+  std::lock_guard<std::mutex> lock(p->mu);
+  LaunchShape &s = t->shape[which];
+  if (s.waves) return s;
+  LaunchShape best{1, 1};
+  int best_res = 0;
+  for (int w = 1; w <= max_waves; w++) {
+    const int b = bytes(w);
+    if (b > t->max_lds) break;
+    int bpc = std::min(t->lds_per_cu / b, 32 / w);
+    const int nb = per_cu(w);
+    if (nb > 0) bpc = std::min(bpc, nb);
+    const int res = std::min(bpc * w, 32);
+    if (res > best_res) {
+      best_res = res;
+      best = LaunchShape{w, bpc};
+    }
+  }
+  return s = best;
+}
+
 }  // namespace
 }  // namespace taccl
 
@@ -176,30 +203,26 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     g.valid = d_valid;
     g.n = n;
     if (!wave) {
-      const int nb = std::max(1, path_greedy_block_per_cu(g));
-      const int bgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * nb);
+      // the block kernel has one size: only its resident blocks are asked for
+      const LaunchShape sh = launch_shape(
+          p, t, kShapePathGreedyBlock, 1, [&](int) { return g.block_bytes; },
+          [&](int) { return path_greedy_block_per_cu(g); });
+      const int bgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
       e = launch_path_greedy_block(g, bgrid, s);
       if (e != hipSuccess) return hip_fail(e, "kernel launch");
       return TACCL_OK;
     }
     // wavefronts per block: most resident wavefronts per CU
-    int best_w = 1, best_res = 0, best_bpc = 1;
-    for (int w = 1; w <= kTreeMaxThreads / 64; w++) {
-      const int bytes = g.o_wave + w * g.wave_bytes;
-      if (bytes > t->max_lds) break;
-      g.waves_per_block = w;
-      int bpc = std::min(t->lds_per_cu / bytes, 32 / w);
-      const int nb = path_greedy_blocks_per_cu(g);
-      if (nb > 0) bpc = std::min(bpc, nb);
-      if (bpc * w > best_res) {
-        best_res = bpc * w;
-        best_w = w;
-        best_bpc = bpc;
-      }
-    }
-    g.waves_per_block = best_w;
-    const int64_t want = (n + best_w - 1) / best_w;
-    const int ggrid = (int)std::min<int64_t>(want, (int64_t)std::max(t->num_cus, 1) * best_bpc);
+    const LaunchShape sh = launch_shape(
+        p, t, kShapePathGreedy, kTreeMaxThreads / 64,
+        [&](int w) { return g.o_wave + w * g.wave_bytes; },
+        [&](int w) {
+          g.waves_per_block = w;
+          return path_greedy_blocks_per_cu(g);
+        });
+    g.waves_per_block = sh.waves;
+    const int64_t want = (n + sh.waves - 1) / sh.waves;
+    const int ggrid = (int)std::min<int64_t>(want, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
     e = launch_path_greedy(g, ggrid, s);
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return TACCL_OK;
@@ -244,10 +267,10 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     const int cpt = p->path_fast ? path_fast_cpt(*p) : 0;
     if (cpt && path_fast_layout(*p, a) <= t->max_lds) {
       const int nt = path_fast_threads(*p);
-      int bpc = std::max(1, std::min(t->lds_per_cu / a.lds_bytes, 4));
-      const int nb = path_fast_blocks_per_cu(a, cpt, nt);
-      if (nb > 0) bpc = std::min(bpc, nb);
-      const int fgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * bpc);
+      const LaunchShape sh = launch_shape(
+          p, t, kShapePathFast, 1, [&](int) { return a.lds_bytes; },
+          [&](int) { return std::min(4, path_fast_blocks_per_cu(a, cpt, nt)); });
+      const int fgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
       e = launch_path_fast(a, cpt, nt, fgrid, s);
     } else {
       if (path_layout(*p, a) > t->max_lds)
@@ -301,27 +324,19 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     // wavefronts per block: most resident wavefronts per CU (LDS, and for
     // the layered kernel registers too, by the runtime's occupancy query)
     auto launch = [&](TreeArgs &x) {
-      int best_w = 1, best_res = 0, best_bpc = 1;
-      for (int w = 1; w <= kTreeMaxThreads / 64; w++) {
-        const int bytes = tree_block_bytes(x, w);
-        if (bytes > t->max_lds) break;
-        int bpc = std::min(t->lds_per_cu / bytes, 32 / w);
-        if (layered) {
-          x.waves_per_block = w;
-          const int nb = greedy ? tree_greedy_blocks_per_cu(x) : tree_layers_blocks_per_cu(x);
-          if (nb > 0) bpc = std::min(bpc, nb);
-        }
-        const int res = std::min(bpc * w, 32);
-        if (res > best_res) {
-          best_res = res;
-          best_w = w;
-          best_bpc = bpc;
-        }
-      }
-      x.waves_per_block = best_w;
-      const int64_t want = (n + best_w - 1) / best_w;
+      const ShapeOf which = layered ? (x.reduce ? kShapeLayersReduce : kShapeLayers)
+                                    : (x.reduce ? kShapeTreeReduce : kShapeTree);
+      const LaunchShape sh = launch_shape(
+          p, t, which, kTreeMaxThreads / 64, [&](int w) { return tree_block_bytes(x, w); },
+          [&](int w) {
+            if (!layered) return 0;
+            x.waves_per_block = w;
+            return greedy ? tree_greedy_blocks_per_cu(x) : tree_layers_blocks_per_cu(x);
+          });
+      x.waves_per_block = sh.waves;
+      const int64_t want = (n + sh.waves - 1) / sh.waves;
       const int tgrid =
-          (int)std::min<int64_t>(want, (int64_t)std::max(t->num_cus, 1) * best_bpc);
+          (int)std::min<int64_t>(want, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
       if (!layered) return launch_tree(x, tgrid, s);
       return greedy ? launch_tree_greedy(x, tgrid, s) : launch_tree_layers(x, tgrid, s);
     };
@@ -334,27 +349,19 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     const bool ranked = !greedy && a.routes_word_aligned && t->rank_img &&
                         tree_rank_layout(*p, ra) > 0 && tree_block_bytes(ra, 1) <= t->max_lds;
     ra.rank_img = (const uint4 *)t->rank_img;
-    const bool ranked_rs = ranked && tree_rank_reverse_ok(*p);
+    const bool ranked_rs = ranked && p->rank_rs_ok;
     auto launch_ranked = [&](TreeArgs &x) {
-      int best_w = 1, best_res = 0, best_bpc = 1;
-      for (int w = 1; w <= kRankMaxThreads / 64; w++) {
-        const int bytes = tree_block_bytes(x, w);
-        if (bytes > t->max_lds) break;
-        int bpc = std::min(t->lds_per_cu / bytes, 32 / w);
-        x.waves_per_block = w;
-        const int nb = tree_rank_blocks_per_cu(x);
-        if (nb > 0) bpc = std::min(bpc, nb);
-        const int res = std::min(bpc * w, 32);
-        if (res > best_res) {
-          best_res = res;
-          best_w = w;
-          best_bpc = bpc;
-        }
-      }
-      x.waves_per_block = best_w;
-      const int64_t want = (n + best_w - 1) / best_w;
+      const LaunchShape sh = launch_shape(
+          p, t, x.reduce ? kShapeRankReduce : kShapeRank, kRankMaxThreads / 64,
+          [&](int w) { return tree_block_bytes(x, w); },
+          [&](int w) {
+            x.waves_per_block = w;
+            return tree_rank_blocks_per_cu(x);
+          });
+      x.waves_per_block = sh.waves;
+      const int64_t want = (n + sh.waves - 1) / sh.waves;
       const int tgrid =
-          (int)std::min<int64_t>(want, (int64_t)std::max(t->num_cus, 1) * best_bpc);
+          (int)std::min<int64_t>(want, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
       return launch_tree_rank(x, tgrid, s);
     };
     if (kind == TACCL_ALLREDUCE) {

@@ -955,7 +955,10 @@ taccl_status_t taccl_sketch_apply(taccl_topology_t topo, taccl_collective_t coll
     if (p->H > 255)
       return fail(TACCL_ERR_UNSUPPORTED, "multicast evaluation holds paths of at most 255 hops");
   }
-  if (coll->kind != TACCL_ALLTOALL && !p->greedy) p->rank_img = tree_rank_image(*p);
+  if (coll->kind != TACCL_ALLTOALL && !p->greedy) {
+    p->rank_img = tree_rank_image(*p);
+    p->rank_rs_ok = tree_rank_reverse_ok(*p);
+  }
   // on-chip bytes of one block (of one wavefront, where blocks hold
   // several) of the kernel the plan runs on, as the launch picks it
   if (coll->kind == TACCL_ALLTOALL) {

@@ -41,6 +41,16 @@ struct taccl_collective {
 
 namespace taccl {
 
+// A kernel's launch shape on one device: wavefronts per block and resident
+// blocks per CU (0: not yet computed).
+struct LaunchShape {
+  int waves = 0, per_cu = 0;
+};
+// the kernels a plan may launch, each with a shape of its own
+enum ShapeOf { kShapeTree, kShapeTreeReduce, kShapeLayers, kShapeLayersReduce, kShapeRank,
+               kShapeRankReduce, kShapePathGreedy, kShapePathGreedyBlock, kShapePathFast,
+               kNumShapes };
+
 // Device copies of the read-only plan tables (one set per device).
 struct DeviceTables {
   void *block = nullptr;  // one allocation holding every table
@@ -70,6 +80,10 @@ struct DeviceTables {
   const uint32_t *arec = nullptr, *cpath = nullptr, *cinfo = nullptr, *cbkt = nullptr;
   const uint32_t *gkrank = nullptr;
   const uint32_t *cn_rec = nullptr, *cn_chunk = nullptr;
+  // Depends on the plan and the device alone, so it is worked out on first
+  // use and kept (under the plan's mutex): the runtime's occupancy query for
+  // every block size cost 2-3 us on each call
+  LaunchShape shape[kNumShapes];
   int max_lds = 0;  // bytes of LDS a block may use on this device
   int lds_per_cu = 0;
   int num_cus = 0;
@@ -133,6 +147,7 @@ struct taccl_plan {
   // large or too dense for 11-bit codes)
   uint64_t pq_magic = 0;
   int32_t pq_range = 0;
+  bool rank_rs_ok = false;  // the ranked kernel may run the ReduceScatter
 
   // Alltoall (path) evaluation: levels of equal remaining cost
   int32_t nlev = 0, ncls = 0, max_lvl_cls = 0, max_lvl_sends = 0;
