@@ -52,7 +52,7 @@ taccl_status_t ensure_device(taccl_plan *p, DeviceTables **out) {
          o_lal = pk.add(p->lalpha), o_lbs = pk.add(p->lbs), o_lmg = pk.add(p->lmerge),
          o_lrev = pk.add(p->lrev), o_hc2 = pk.add(p->hop_class2),
          o_lcb2 = pk.add(p->lvl_cls2_begin), o_llc2 = pk.add(p->llc2),
-         o_gkr = pk.add(p->gkrank), o_rimg = pk.add(p->rank_img), o_c2l = pk.add(p->cls2_link),
+         o_gkr = pk.add(p->gkrank), o_rimg = pk.add(p->rank_img), o_tent = pk.add(p->tent), o_c2l = pk.add(p->cls2_link),
          o_cnr = pk.add(p->cn_rec), o_cnc = pk.add(p->cn_chunk);
   void *blk = nullptr;
   e = hipMalloc(&blk, pk.bytes.size());
@@ -95,6 +95,7 @@ taccl_status_t ensure_device(taccl_plan *p, DeviceTables **out) {
   t.cinfo = (const uint32_t *)at(o_cinfo);
   t.cbkt = (const uint32_t *)at(o_cbkt);
   t.gkrank = (const uint32_t *)at(o_gkr);
+  t.tent = (const uint8_t *)at(o_tent);
   t.rank_img = p->rank_img.empty() ? nullptr : at(o_rimg);
   t.cn_rec = p->cn_rec.empty() ? nullptr : (const uint32_t *)at(o_cnr);
   t.cn_chunk = (const uint32_t *)at(o_cnc);
@@ -346,13 +347,14 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     // the ReduceScatter (alone or as an Allreduce's first phase) when every
     // route hop has a reverse link of equal cost and there is no contiguity
     TreeArgs ra = a;
-    const bool ranked = !greedy && a.routes_word_aligned && t->rank_img &&
+    const bool ranked = !greedy && t->rank_img &&
                         tree_rank_layout(*p, ra) > 0 && tree_block_bytes(ra, 1) <= t->max_lds;
     ra.rank_img = (const uint4 *)t->rank_img;
+    ra.ent = t->tent;
     const bool ranked_rs = ranked && p->rank_rs_ok;
     auto launch_ranked = [&](TreeArgs &x) {
       const LaunchShape sh = launch_shape(
-          p, t, x.reduce ? kShapeRankReduce : kShapeRank, kRankMaxThreads / 64,
+          p, t, x.reduce ? kShapeRankReduce : kShapeRank, tree_rank_max_waves(x),
           [&](int w) { return tree_block_bytes(x, w); },
           [&](int w) {
             x.waves_per_block = w;

@@ -68,10 +68,23 @@ __device__ __forceinline__ uint32_t max_dpp(uint32_t v) {
   return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, Ctrl, RowMask, 0xf, true));
 }
 
-// Route word j (route bytes of chunk j / PW) as one-hot option bytes:
+// Largest block (threads) of the instantiation with J slots per lane: up to
+// 8 slots, 12 wavefronts (168 registers each); beyond, 8 wavefronts (256
+// registers: the per-slot state would spill at 168).
+template <int J>
+constexpr int rank_max_threads() {
+  return J <= 8 ? kRankMaxThreads : 512;
+}
+
+// Four route bytes from any byte address in one load
+typedef uint32_t __attribute__((aligned(1))) u32_any;
+
+// Route word j (route bytes of chunk j / PW, padded to PW words) as one-hot
+// option bytes:
 // 1 << choice, 0 for a choice of 8 or more (no pair of these plans has as
 // many options, so such a choice leaves the pair unrouted) and 0 for a
-// destination outside the chunk's postcondition (never routed).
+// destination outside the chunk's postcondition (never routed; also the
+// padding past rank P - 1, whatever bytes it holds).
 template <int PW>
 __device__ __forceinline__ uint32_t one_hot(uint32_t w, uint32_t j, const uint64_t *s_post) {
   const uint32_t pm4 = (uint32_t)(s_post[j / PW] >> (4 * (j % PW))) & 0xFu;
@@ -90,7 +103,7 @@ __device__ __forceinline__ uint32_t one_hot(uint32_t w, uint32_t j, const uint64
 // length = longest reversed path from below up to v; a send is ready when
 // every send into v has finished)
 template <int J, int PW, bool kC, bool kR>
-__global__ __launch_bounds__(kRankMaxThreads) void tree_rank_kernel(TreeArgs a) {
+__global__ __launch_bounds__(rank_max_threads<J>()) void tree_rank_kernel(TreeArgs a) {
   static_assert(!(kC && kR), "contiguous transfers are not combined with ReduceScatter here");
   extern __shared__ __align__(16) unsigned char lds[];
   const int C = a.C, V = a.V, E = a.E, K = a.K;
@@ -105,7 +118,12 @@ __global__ __launch_bounds__(kRankMaxThreads) void tree_rank_kernel(TreeArgs a) 
   // owner, so that the 16 lanes of a row (one chunk, consecutive vertices)
   // read 16 banks and two owners fall on different halves
   uint32_t *s_opt = (uint32_t *)(lds + a.o_opt);
-  uint8_t *s_ent = lds + a.o_ent;  // entering link per (o, v, d, k)
+  // entering link per (o, v, d, k). Past 8 slots per lane the table (P * V *
+  // P * K bytes: 41 KB at 24 ranks) stays in global memory, where the L2
+  // holds it: in LDS it left room for 2 to 6 wavefronts per CU, and those
+  // plans are bound by the wavefronts in flight
+  constexpr bool kEntLds = J <= 8;
+  const uint8_t *s_ent = kEntLds ? (const uint8_t *)(lds + a.o_ent) : a.ent;
   // per slot: entering-link table base | chunk's first slot << 20 | root <<
   // 30 | in the postcondition << 31, and option base | route word base << 16
   // | owner << 24
@@ -137,7 +155,12 @@ __global__ __launch_bounds__(kRankMaxThreads) void tree_rank_kernel(TreeArgs a) 
 
   const int64_t stride = (int64_t)gridDim.x * a.waves_per_block;
   const int64_t first = (int64_t)blockIdx.x * a.waves_per_block + wave;
-  const int nrw = a.route_stride >> 2;
+  // A chunk's row of P route bytes takes PW words; with P below 4 PW a word
+  // starts pad bytes earlier per chunk before it than its index says, and the
+  // words that would reach past the candidate's row are read from the row's
+  // last four bytes and shifted down when staged.
+  const int nrw = C * PW, pad = 4 * PW - a.P;
+  auto route_offset = [&](int j) -> int { return pad ? 4 * j - pad * (j / PW) : 4 * j; };
   // The next candidate's route words are loaded as soon as this one's are
   // staged, and its priorities as soon as this one's are folded into keys,
   // so both arrive while this candidate is evaluated and only one set of
@@ -145,11 +168,13 @@ __global__ __launch_bounds__(kRankMaxThreads) void tree_rank_kernel(TreeArgs a) 
   uint32_t pf_r[kPfRouteWords], px[J];
   auto load_routes = [&](int64_t i, int ln) {
     if (i >= a.n) return;
-    const uint32_t *g32 = (const uint32_t *)(a.routes + (size_t)i * a.route_stride);
+    const uint8_t *row = a.routes + (size_t)i * a.route_stride;
 #pragma unroll
     for (int k = 0; k < kPfRouteWords; k++) {
       const int j = ln + 64 * k;
-      if (j < nrw) pf_r[k] = __builtin_nontemporal_load(g32 + j);
+      if (j < nrw)
+        pf_r[k] = __builtin_nontemporal_load(
+            (const u32_any *)(row + min(route_offset(j), a.route_stride - 4)));
     }
   };
   auto load_prio = [&](int64_t i, int ln) {
@@ -190,7 +215,11 @@ __global__ __launch_bounds__(kRankMaxThreads) void tree_rank_kernel(TreeArgs a) 
 #pragma unroll
     for (int k = 0; k < kPfRouteWords; k++) {
       const int j = lane + 64 * k;
-      if (j < nrw) rt32[j] = one_hot<PW>(pf_r[k], j, s_post);
+      if (j < nrw) {
+        uint32_t w = pf_r[k];
+        if (pad) w >>= 8 * min(max(route_offset(j) - (a.route_stride - 4), 0), 3);
+        rt32[j] = one_hot<PW>(w, j, s_post);
+      }
     }
     load_routes(i + stride, lane);
     for (int l = lane; l < E; l += 64) lfree[l] = 0;
@@ -204,8 +233,8 @@ __global__ __launch_bounds__(kRankMaxThreads) void tree_rank_kernel(TreeArgs a) 
     uint32_t pl[J], an[J], acc[J];
     uint32_t bad = 0, fault = 0;
 #pragma unroll
-    for (int g0 = 0; g0 < J; g0 += 2) {
-      constexpr int G = J < 2 ? J : 2;
+    for (int g0 = 0; g0 < J; g0 += (J < 2 ? J : J <= 8 || J % 4 ? 2 : 4)) {
+      constexpr int G = J < 2 ? J : kEntLds || J % 4 ? 2 : 4;
       uint32_t slc[G], pos[G];
       uint2 si[G];
 #pragma unroll
@@ -253,10 +282,13 @@ __global__ __launch_bounds__(kRankMaxThreads) void tree_rank_kernel(TreeArgs a) 
         // its own), then selected
         // 24-bit multiplies (d < 64, K <= 8) issue at the full VALU rate
         const uint32_t ei = ((si[q].x & 0xFFFFFu) + __umul24(d, (uint32_t)K) + kd) & (0u - has);
-        uint32_t le = s_ent[ei];
-        asm volatile("" : "+v"(le));
-        l[q] = has ? le : 0xFFu;
+        l[q] = s_ent[ei];
         pos[q] = has;
+      }
+#pragma unroll
+      for (int q = 0; q < G; q++) {
+        asm volatile("" : "+v"(l[q]));
+        l[q] = pos[q] ? l[q] : 0xFFu;
       }
 #pragma unroll
       for (int q = 0; q < G; q++) {
@@ -636,16 +668,31 @@ __global__ __launch_bounds__(kRankMaxThreads) void tree_rank_kernel(TreeArgs a) 
 
 int32_t align16(int32_t x) { return (x + 15) & ~15; }
 
+// Route words per chunk of the instantiation that runs P ranks
+int rank_words(int P) {
+  const int w = (P + 3) / 4;
+  return w == 5 ? 6 : w == 7 ? 8 : w;
+}
+
+// Slots per lane of the instantiation that runs C * V slots
+int rank_slots_per_lane(int cv) {
+  const int j = (cv + 63) / 64;
+  return j <= 2 ? std::max(j, 1) : j <= 4 ? 4 : j <= 6 ? 6 : j <= 8 ? 8 : j <= 10 ? 10 : j <= 12 ? 12 : j <= 14 ? 14 : 16;
+}
+
 template <int J, bool kC, bool kR>
 const void *rank_fn_jc(int pw) {
   switch (pw) {
-    case 1: return (const void *)tree_rank_kernel<J, 1, kC, kR>;
-    case 2: return (const void *)tree_rank_kernel<J, 2, kC, kR>;
     case 3: return (const void *)tree_rank_kernel<J, 3, kC, kR>;
     case 4: return (const void *)tree_rank_kernel<J, 4, kC, kR>;
     case 6: return (const void *)tree_rank_kernel<J, 6, kC, kR>;
-    default: return (const void *)tree_rank_kernel<J, 8, kC, kR>;
+    case 8: return (const void *)tree_rank_kernel<J, 8, kC, kR>;
   }
+  if constexpr (J <= 8) {
+    if (pw == 1) return (const void *)tree_rank_kernel<J, 1, kC, kR>;
+    if (pw == 2) return (const void *)tree_rank_kernel<J, 2, kC, kR>;
+  }
+  return nullptr;
 }
 
 // ReduceScatter never runs with contiguous transfers here
@@ -655,19 +702,19 @@ const void *rank_fn_j(int pw, bool contig, bool reduce) {
   return contig ? rank_fn_jc<J, true, false>(pw) : rank_fn_jc<J, false, false>(pw);
 }
 
-// slots per lane of the instantiation that runs C * V <= 512 slots
-int rank_slots_per_lane(int cv) {
-  const int j = (cv + 63) / 64;
-  return j <= 1 ? 1 : j <= 2 ? 2 : j <= 4 ? 4 : 8;
-}
-
 const void *rank_fn(const TreeArgs &a) {
-  const int pw = a.P / 4;
+  const int pw = rank_words(a.P);
+  const bool c = a.contig != 0, r = a.reduce != 0;
   switch (rank_slots_per_lane(a.C * a.V)) {
-    case 1: return rank_fn_j<1>(pw, a.contig != 0, a.reduce != 0);
-    case 2: return rank_fn_j<2>(pw, a.contig != 0, a.reduce != 0);
-    case 4: return rank_fn_j<4>(pw, a.contig != 0, a.reduce != 0);
-    default: return rank_fn_j<8>(pw, a.contig != 0, a.reduce != 0);
+    case 1: return rank_fn_j<1>(pw, c, r);
+    case 2: return rank_fn_j<2>(pw, c, r);
+    case 4: return rank_fn_j<4>(pw, c, r);
+    case 6: return rank_fn_j<6>(pw, c, r);
+    case 8: return rank_fn_j<8>(pw, c, r);
+    case 10: return rank_fn_j<10>(pw, c, r);
+    case 12: return rank_fn_j<12>(pw, c, r);
+    case 14: return rank_fn_j<14>(pw, c, r);
+    default: return rank_fn_j<16>(pw, c, r);
   }
 }
 
@@ -677,11 +724,17 @@ int32_t tree_rank_layout(const taccl_plan &p, TreeArgs &a) {
   const int32_t C = p.coll.C, V = p.topo.V, E = p.topo.E, P = p.topo.P;
   const int32_t CV = C * V;
   const int32_t K = std::max(p.max_paths, 1), H = std::max(p.H, 1);
-  const int32_t pw = P / 4;
+  const int32_t pw = rank_words(P);
+  // Any rank count up to 32 and any route length (entering links come from a
+  // table per vertex and option): wherever both fit, this kernel took 0.11 to
+  // 0.43 of the general kernel's time (9999 candidates on three 8-rank
+  // meshes 342 -> 106 us, 4000 on a 30-rank ring 511 -> 117 us, 20000
+  // Allreduces on 14 ranks 889 -> 378 us). Past 512 slots only chunks of 9 ranks or
+  // more (3 route words) are instantiated; staged route words and a slot's
+  // word base bound the chunks (256 words).
   if (p.coll.kind == TACCL_ALLTOALL || p.topt.empty() || p.tent.empty() || p.pq_range <= 0 ||
-      K > 8 || H > 4 || P % 4 || (pw != 1 && pw != 2 && pw != 3 && pw != 4 && pw != 6 && pw != 8) ||
-      V > 64 || E < 1 || E > 255 || CV > 64 * kLayerMaxSlotsPerLane || p.route_stride > 4 * 64 * kPfRouteWords ||
-      p.route_stride % 4)
+      K > 8 || P > 32 || V > 64 || E < 1 || E > 255 || CV > kRankMaxSlots ||
+      (CV > 512 && pw < 3) || C * pw > 64 * kPfRouteWords || p.route_stride < 4)
     return 0;
   uint64_t cmin = ~0ull, cmax = 0;
   for (uint32_t c : p.cost) {
@@ -689,7 +742,7 @@ int32_t tree_rank_layout(const taccl_plan &p, TreeArgs &a) {
     cmax = std::max<uint64_t>(cmax, c);
   }
   if (cmin == 0 || cmax >= (1u << 24)) return 0;  // link costs: 24-bit multiplies
-  const uint64_t max_rem = (uint64_t)(V - 1) * cmax;
+  const uint64_t max_rem = p.pq_max;  // longest tree path
   if (max_rem >= (1ull << 32)) return 0;
   a.lmagic = ((1ull << 32) + cmin - 1) / cmin;  // ceil(2^32 / c_min)
   if (a.lmagic >= (1ull << 32) || p.pq_magic >= (1ull << 32)) return 0;  // 32-bit multiply-high
@@ -717,7 +770,8 @@ int32_t tree_rank_layout(const taccl_plan &p, TreeArgs &a) {
   // mod 32 (two owners' rows fall on different bank halves)
   a.opt_ostride = pw * V + ((16 - (pw * V) % 32) + 32) % 32;
   a.o_opt = take(4 * P * a.opt_ostride);
-  a.o_ent = take(P * V * P * K);
+  a.o_ent = off;
+  if (CV <= 512) take(P * V * P * K);  // larger plans read it from global memory
   a.o_slot = take(8 * CV);
   if ((int64_t)P * V * P * K >= (1 << 20)) return 0;  // entering-link base: 20 bits
   a.o_wave = off;
@@ -731,8 +785,8 @@ int32_t tree_rank_layout(const taccl_plan &p, TreeArgs &a) {
   // then 8-byte entries (three spare), bounds and u16 parent sends per
   // position; then finish times
   const int32_t CVp = 64 * rank_slots_per_lane(CV);
-  const int32_t tree_bytes = align16(p.route_stride) + align16(8 * CVp) + align16(4 * CVp);
-  a.w_dist = align16(p.route_stride);
+  const int32_t tree_bytes = align16(4 * C * pw) + align16(8 * CVp) + align16(4 * CVp);
+  a.w_dist = align16(4 * C * pw);
   a.w_anc = a.w_dist;
   a.w_h = a.w_dist + align16(8 * CVp);
   const int32_t cnt_bytes = align16(4 * (int32_t)((nl * E + 2) / 2 + 64));
@@ -761,7 +815,8 @@ std::vector<uint8_t> tree_rank_image(const taccl_plan &p) {
   TreeArgs a{};
   const int32_t bytes = tree_rank_layout(p, a);
   if (bytes <= 0 || bytes > 160 * 1024) return {};  // no CU holds it
-  const int32_t C = p.coll.C, V = p.topo.V, E = p.topo.E, P = p.topo.P, K = a.K, PW = P / 4;
+  const int32_t C = p.coll.C, V = p.topo.V, E = p.topo.E, P = p.topo.P, K = a.K,
+                PW = rank_words(P);
   std::vector<uint8_t> img(a.o_wave, 0);
   uint8_t *b = img.data();
   uint32_t *cost = (uint32_t *)(b + a.o_cost), *rcost = (uint32_t *)(b + a.o_rcost);
@@ -780,7 +835,7 @@ std::vector<uint8_t> tree_rank_image(const taccl_plan &p) {
     for (int32_t v = 0; v < V; v++)
       for (int32_t d = 0; d < P; d++)
         opt[4 * (o * a.opt_ostride + d / 4 * V + v) + d % 4] = p.topt[((size_t)o * V + v) * P + d];
-  std::copy(p.tent.begin(), p.tent.end(), b + a.o_ent);
+  if (C * V <= 512) std::copy(p.tent.begin(), p.tent.end(), b + a.o_ent);
   uint32_t *slot = (uint32_t *)(b + a.o_slot);
   for (int32_t c = 0; c < C; c++)
     for (int32_t v = 0; v < V; v++) {
@@ -813,10 +868,13 @@ int tree_rank_blocks_per_cu(const TreeArgs &a) {
   return nb;
 }
 
+int tree_rank_max_waves(const TreeArgs &a) {
+  return (rank_slots_per_lane(a.C * a.V) <= 8 ? rank_max_threads<8>() : rank_max_threads<16>()) / 64;
+}
+
 hipError_t launch_tree_rank(const TreeArgs &a, int grid, hipStream_t stream) {
-  const int pw = a.P / 4;
-  if (a.P % 4 || (pw != 1 && pw != 2 && pw != 3 && pw != 4 && pw != 6 && pw != 8) ||
-      a.C * a.V > 1024 || a.E > 255 || a.qrange <= 0)
+  if (a.P > 32 || a.C * a.V > kRankMaxSlots || a.E > 255 || a.qrange <= 0 || !rank_fn(a) ||
+      a.waves_per_block > tree_rank_max_waves(a))
     return hipErrorInvalidValue;
   const dim3 g(grid), b(64 * a.waves_per_block);
   const int bytes = tree_block_bytes(a, a.waves_per_block);

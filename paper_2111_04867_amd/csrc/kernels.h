@@ -66,6 +66,7 @@ struct TreeArgs {
   uint64_t qmagic;
   int32_t qrange;
   const uint4 *rank_img;  // the block's shared LDS below o_wave, ready to copy
+  const uint8_t *ent;
   int32_t o_rcost, o_ent, w_h, o_slot, opt_ostride, w_pj;
 };
 
@@ -173,11 +174,12 @@ constexpr int kConnWaveThreads = 1024;
 constexpr int kConnRecLdsMax = 64 * 1024;
 
 constexpr int kTreeMaxThreads = 512;  // up to 8 wavefronts per block
-// (chunk, vertex) slots per lane of the layered, greedy and ranked multicast
+// (chunk, vertex) slots per lane of the layered and greedy multicast
 // kernels: at most 8, i.e. C x V <= 512 (beyond that their register state
 // would spill to scratch; larger plans run on the general kernel)
 constexpr int kLayerMaxSlotsPerLane = 8;
 constexpr int kRankMaxThreads = 768;  // ranked multicast kernel: up to 12
+constexpr int kRankMaxSlots = 1024;   // its (chunk, vertex) slots: 16 per lane
 constexpr int kTreeRecLdsMax = 32768;  // route records kept in LDS up to this size
 constexpr int kPathThreads = 256;
 constexpr int kPathPortThreads = 1024;  // LDS-record kernel on switch-port plans
@@ -199,6 +201,7 @@ std::vector<uint8_t> tree_rank_image(const taccl_plan &p);
 // the ranked kernel may run the plan's ReduceScatter (reverse links with
 // equal costs, no contiguity)
 bool tree_rank_reverse_ok(const taccl_plan &p);
+int tree_rank_max_waves(const TreeArgs &a);  // most wavefronts per block
 int tree_rank_blocks_per_cu(const TreeArgs &a);
 hipError_t launch_tree_rank(const TreeArgs &a, int grid, hipStream_t stream);
 // Layered multicast kernel: fills the layout and returns the bytes of a

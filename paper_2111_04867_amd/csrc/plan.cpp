@@ -552,10 +552,41 @@ static taccl_status_t build_levels(taccl_plan *p) {
   return TACCL_OK;
 }
 
+// The most node-crossing links on any path of a chunk's tree, or -1 if the
+// routes do not bound it. When every route from an owner that passes a
+// vertex has crossed the same number of times there, so has the vertex's
+// tree path: its parent hop is a hop of such a route, and by induction the
+// parent's count is the route's count at the parent.
+static int32_t tree_crossings(const taccl_plan *p) {
+  const int32_t P = p->topo.P, V = p->topo.V;
+  const std::vector<int32_t> &node = p->topo.node;
+  int32_t most = 0;
+  std::vector<int32_t> at(V);
+  for (int32_t o = 0; o < P; o++) {
+    std::fill(at.begin(), at.end(), -1);
+    at[o] = 0;
+    for (int32_t d = 0; d < P; d++)
+      for (int32_t k = 0; k < p->npaths[(size_t)o * P + d]; k++) {
+        const uint32_t q = p->pair_base[(size_t)o * P + d] + k;
+        int32_t crossed = 0;
+        for (uint32_t j = p->path_off[q]; j < p->path_off[q + 1]; j++) {
+          const int32_t u = p->lsrc[p->path_links[j]], v = p->ldst[p->path_links[j]];
+          crossed += node[u] != node[v];
+          if (at[v] >= 0 && at[v] != crossed) return -1;
+          at[v] = crossed;
+          most = std::max(most, crossed);
+        }
+      }
+  }
+  return most;
+}
+
 // Codes for the remaining and travelled lengths of multicast sends. Each is
 // the cost of a path of a chunk's tree (at most V - 1 links, every one a
 // hop of some route option), so it lies in S, the set of sums of at most
-// V - 1 costs of such links. With g the smallest gap between two elements
+// V - 1 costs of links inside a node and at most as many crossing links as
+// a tree path can have (V - 1 of any links where the routes do not bound
+// that). With g the smallest gap between two elements
 // of S and m = ceil(2^32 / g), x -> floor(x * m / 2^32) is nondecreasing
 // everywhere and gains at least 1 per step of S (g * m >= 2^32), so it
 // orders and separates S exactly. Left at range 0 when S exceeds 16384
@@ -563,22 +594,36 @@ static taccl_status_t build_levels(taccl_plan *p) {
 static void path_sum_codes(taccl_plan *p) {
   p->pq_magic = 0;
   p->pq_range = 0;
-  std::vector<uint64_t> costs;
-  for (uint16_t l : p->path_links) costs.push_back(p->cost[l]);
-  std::sort(costs.begin(), costs.end());
-  costs.erase(std::unique(costs.begin(), costs.end()), costs.end());
-  if (costs.empty() || costs[0] == 0) return;
-  std::vector<uint64_t> S{0}, next;
-  for (int32_t step = 0; step < p->topo.V - 1; step++) {
-    next = S;
-    for (uint64_t s : S)
-      for (uint64_t c : costs) next.push_back(s + c);
-    std::sort(next.begin(), next.end());
-    next.erase(std::unique(next.begin(), next.end()), next.end());
-    if (next.size() > 16384) return;
-    if (next.size() == S.size()) break;  // closed: no longer sums appear
-    S.swap(next);
+  p->pq_max = 0;
+  const int32_t cross = tree_crossings(p);
+  std::vector<uint64_t> inside, between;
+  for (uint16_t l : p->path_links) {
+    const bool x = cross >= 0 && p->topo.node[p->lsrc[l]] != p->topo.node[p->ldst[l]];
+    (x ? between : inside).push_back(p->cost[l]);
   }
+  auto distinct = [](std::vector<uint64_t> &v) {
+    std::sort(v.begin(), v.end());
+    v.erase(std::unique(v.begin(), v.end()), v.end());
+  };
+  distinct(inside);
+  distinct(between);
+  if (inside.empty() && between.empty()) return;
+  if ((!inside.empty() && inside[0] == 0) || (!between.empty() && between[0] == 0)) return;
+  std::vector<uint64_t> S{0}, next;
+  // S with up to `times` elements of `costs` added; false past 16384 sums
+  auto add = [&](const std::vector<uint64_t> &costs, int32_t times) {
+    for (int32_t step = 0; step < times; step++) {
+      next = S;
+      for (uint64_t s : S)
+        for (uint64_t c : costs) next.push_back(s + c);
+      distinct(next);
+      if (next.size() > 16384) return false;
+      if (next.size() == S.size()) break;  // closed: no longer sums appear
+      S.swap(next);
+    }
+    return true;
+  };
+  if (!add(inside, p->topo.V - 1) || !add(between, cross >= 0 ? cross : 0)) return;
   if (S.back() >= (1ull << 32)) return;
   uint64_t gap = ~0ull;
   for (size_t i = 1; i < S.size(); i++) gap = std::min(gap, S[i] - S[i - 1]);
@@ -591,6 +636,7 @@ static void path_sum_codes(taccl_plan *p) {
   if (range > 2048) return;
   p->pq_magic = m;
   p->pq_range = (int32_t)range;
+  p->pq_max = S.back();
 }
 
 // Tables of the wavefront-per-candidate connection count: the switched rank

@@ -66,7 +66,7 @@ struct DeviceTables {
   const uint8_t *owner8 = nullptr;
   const uint8_t *topt = nullptr;
   const uint32_t *tree_rec4 = nullptr;
-  const uint8_t *rank_img = nullptr;
+  const uint8_t *rank_img = nullptr, *tent = nullptr;
   const uint32_t *lalpha = nullptr;
   const uint64_t *lbs = nullptr;
   const uint8_t *lmerge = nullptr;
@@ -147,6 +147,7 @@ struct taccl_plan {
   // large or too dense for 11-bit codes)
   uint64_t pq_magic = 0;
   int32_t pq_range = 0;
+  uint64_t pq_max = 0;  // the largest such sum
   bool rank_rs_ok = false;  // the ranked kernel may run the ReduceScatter
 
   // Alltoall (path) evaluation: levels of equal remaining cost

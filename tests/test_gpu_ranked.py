@@ -1,0 +1,128 @@
+"""GPU parity of the ranked multicast kernel at the edges of what it takes:
+rank counts that do not fill their last route word, routes longer than four
+links, (chunk, vertex) slot counts around each slots-per-lane step up to
+1024, rows that are not word aligned, and path codes that rest on the number
+of node crossings. Bit for bit against the oracle. Needs an MI355X."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+from oracle import OraclePlan
+from workloads import configs as cf
+from workloads import generate
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2111_04867_amd import binding
+    binding.lib()
+    torch.cuda.set_device(0)
+    yield
+
+
+def ring(P, k=2, cpr=1, chunk_bytes=65536):
+    row_ptr, col, a, b = cf.csr_from_edges(P, cf.ring_edges(list(range(P)), 700, 46))
+    return cf.Workload(f"ring{P}x{cpr}", P, P, row_ptr, col, a, b, None, cf.ALLGATHER, cpr,
+                       chunk_bytes, cf.KSHORTEST, k=k)
+
+
+def broadcast(base, C):
+    """C chunks from ranks 0, 1, ... to every rank."""
+    return cf.explicit_multicast(base, [c % base.P for c in range(C)],
+                                 [list(range(base.P))] * C)
+
+
+def check(w, n=65, seed=3, shift=0):
+    from paper_2111_04867_amd.binding import Plan
+    plan, ref = Plan.from_workload(w), OraclePlan.from_workload(w)
+    opts = plan.route_options()
+    assert (opts == ref.route_options()).all()
+    routes, prio = generate(seed, 0, n, opts, plan.prio_stride)
+    rng = np.random.default_rng(seed)
+    routes[rng.random(routes.shape) < 0.01] = 0xFF  # some pairs unrouted
+    prio[rng.random(prio.shape) < 0.3] &= 3         # and equal priorities
+    print(f"[gpu] ranked {w.name} kind={w.kind} contig={w.contiguity} P={plan.P} "
+          f"slots={plan.num_chunks * plan.V} hops={plan.max_hops} shift={shift}", flush=True)
+    buf = torch.full((routes.size + shift,), 7, dtype=torch.uint8, device="cuda")
+    buf[shift:] = torch.from_numpy(routes.reshape(-1))
+    pr = torch.from_numpy(prio.view(np.int32)).cuda()
+    mk = torch.empty(n, dtype=torch.int32, device="cuda")
+    ok = torch.empty(n, dtype=torch.uint8, device="cuda")
+    plan.eval_tensors(buf[shift:].view(n, -1), pr, mk, ok)
+    torch.cuda.synchronize()
+    rmk, rok = ref.eval(routes, prio)
+    assert np.array_equal(mk.cpu().numpy().view(np.uint32), rmk), w.name
+    assert np.array_equal(ok.cpu().numpy(), rok), w.name
+
+
+def kinds(w):
+    yield w
+    yield cf.as_reduction(w, cf.REDUCESCATTER)
+    yield cf.as_reduction(w, cf.ALLREDUCE)
+
+
+@pytest.mark.parametrize("P", [3, 4, 5, 6, 7, 9, 11, 13, 17, 18, 21, 25, 29, 31, 32])
+def test_rank_counts_and_long_routes(P):
+    for w in kinds(ring(P)):  # routes of up to P - 1 links
+        check(w, n=33 if P > 16 else 65)
+
+
+@pytest.mark.parametrize("P", [5, 7, 10, 14, 17])
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+def test_unaligned_rows(P, shift):
+    check(cf.full_ag(P, k=3), n=17, shift=shift)
+
+
+def test_word_aligned_ranks_behind_an_odd_pointer():
+    for shift in (1, 2):
+        check(cf.cubemesh8_ag(), n=70, shift=shift)
+
+
+# slots per lane 1, 2, 4, 6, 8, 10 and 16, first and last slot count of each
+@pytest.mark.parametrize("P,C", [(8, 8), (9, 8), (16, 8), (13, 10), (16, 16), (17, 16), (24, 16),
+                                 (11, 35), (16, 32), (27, 19), (20, 32), (23, 28), (32, 32),
+                                 (9, 85), (12, 85)])
+def test_slot_counts(P, C):
+    w = broadcast(cf.full_ag(P, k=2), C)
+    check(w, n=40)
+
+
+@pytest.mark.parametrize("per,cpr,kib", [(3, 1, 17), (4, 2, 1000), (5, 1, 333), (6, 2, 64),
+                                         (6, 1, 4)])
+@pytest.mark.parametrize("contiguity", [0, 1])
+def test_two_nodes(per, cpr, kib, contiguity):
+    """Two link costs whose sums are only told apart when each path crosses
+    between the nodes at most once."""
+    w = replace(cf.two_node_full(per, cf.ALLGATHER, cpr, k=3, chunk_bytes=1024 * kib,
+                                 contiguity=contiguity), max_cross=1,
+                relay=np.ones(2 * per, dtype=np.uint8))
+    check(w, n=40)
+    if not contiguity:
+        for x in kinds(w):
+            check(x, n=40)
+
+
+def test_three_mesh_nodes():
+    """24 ranks on three cube-meshes joined between relays: 576 slots."""
+    P = V = 24
+    edges = []
+    for n in range(3):
+        edges += cf.cube_mesh_edges(8 * n, cf.NVLINK_ALPHA, cf.NDV2_NVLINK_BETA)
+    relays = [8 * n + r for n in range(3) for r in (0, 4)]
+    edges += [(s, d, cf.IB_ALPHA, cf.IB_BETA) for s in relays for d in relays if s // 8 != d // 8]
+    row_ptr, col, a, b = cf.csr_from_edges(V, edges)
+    relay = np.zeros(V, dtype=np.uint8)
+    relay[relays] = 1
+    w = cf.Workload("threenode24_ag", V, P, row_ptr, col, a, b,
+                    np.array([r // 8 for r in range(V)], dtype=np.int32), cf.ALLGATHER, 1, 1 << 20,
+                    cf.KSHORTEST, k=3, max_cross=1, relay=relay)
+    for x in kinds(w):
+        check(x, n=150)
+    check(cf.with_contiguity(w), n=150)
