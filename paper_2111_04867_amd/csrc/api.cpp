@@ -53,7 +53,8 @@ taccl_status_t ensure_device(taccl_plan *p, DeviceTables **out) {
          o_lrev = pk.add(p->lrev), o_hc2 = pk.add(p->hop_class2),
          o_lcb2 = pk.add(p->lvl_cls2_begin), o_llc2 = pk.add(p->llc2),
          o_gkr = pk.add(p->gkrank), o_rimg = pk.add(p->rank_img), o_tent = pk.add(p->tent), o_c2l = pk.add(p->cls2_link),
-         o_cnr = pk.add(p->cn_rec), o_cnc = pk.add(p->cn_chunk);
+         o_cnr = pk.add(p->cn_rec), o_cnc = pk.add(p->cn_chunk),
+         o_plfb = pk.add(p->ports_lfb), o_pwalk = pk.add(p->pwalk), o_pport = pk.add(p->pport);
   void *blk = nullptr;
   e = hipMalloc(&blk, pk.bytes.size());
   if (e != hipSuccess) return fail(TACCL_ERR_NO_MEMORY, "hipMalloc of plan tables failed");
@@ -97,6 +98,9 @@ taccl_status_t ensure_device(taccl_plan *p, DeviceTables **out) {
   t.gkrank = (const uint32_t *)at(o_gkr);
   t.tent = (const uint8_t *)at(o_tent);
   t.rank_img = p->rank_img.empty() ? nullptr : at(o_rimg);
+  t.ports_lfb = (const uint32_t *)at(o_plfb);
+  t.pwalk = (const uint32_t *)at(o_pwalk);
+  t.pport = (const uint16_t *)at(o_pport);
   t.cn_rec = p->cn_rec.empty() ? nullptr : (const uint32_t *)at(o_cnr);
   t.cn_chunk = (const uint32_t *)at(o_cnc);
   t.max_lds = (int)prop.sharedMemPerBlock;
@@ -228,7 +232,34 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return TACCL_OK;
   }
-  if (p->coll.kind == TACCL_ALLTOALL) {
+  PortsArgs pa{};
+  if (p->ports && path_ports_layout(*p, pa) > 0 && pa.lds_bytes <= t->max_lds &&
+      path_ports_supported(*p, t->max_lds)) {
+    pa.C = p->coll.C;
+    pa.H = std::max(p->H, 1);
+    pa.nlev = p->nlev;
+    pa.route_stride = p->route_stride;
+    pa.prio_stride = p->prio_stride;
+    pa.routes_words = (p->route_stride % 4 == 0) && (((uintptr_t)d_routes & 3) == 0);
+    pa.cost = t->cost;
+    pa.arec = t->arec;
+    pa.cpath = t->cpath;
+    pa.cinfo = t->cinfo;
+    pa.cbkt = t->cbkt;
+    pa.lfb = t->ports_lfb;
+    pa.pwalk = t->pwalk;
+    pa.pport = t->pport;
+    pa.routes = d_routes;
+    pa.prio = d_prio;
+    pa.makespan = d_makespan;
+    pa.valid = d_valid;
+    pa.n = n;
+    const LaunchShape sh = launch_shape(
+        p, t, kShapePathPorts, 1, [&](int) { return pa.lds_bytes; },
+        [&](int) { return path_ports_blocks_per_cu(pa); });
+    const int pgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
+    e = launch_path_ports(pa, pgrid, s);
+  } else if (p->coll.kind == TACCL_ALLTOALL) {
     PathArgs a{};
     a.C = p->coll.C;
     a.P = p->topo.P;
@@ -276,7 +307,7 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     } else {
       if (path_layout(*p, a) > t->max_lds)
         return fail(TACCL_ERR_UNSUPPORTED, "Alltoall plan needs more LDS than a block has");
-      if (a.ports && a.E > 4 * a.lr_threads)
+      if (a.ports && !path_ports_supported(*p, t->max_lds))
         return fail(TACCL_ERR_UNSUPPORTED, "switch ports take at most four links per thread");
       e = launch_path(a, grid, s);
     }

@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "path_sort.h"
 #include "wave.h"
 
 namespace taccl {
@@ -72,22 +73,6 @@ __device__ __forceinline__ uint32_t lds_get(uint32_t *p) {
 }
 __device__ __forceinline__ void lds_put(uint32_t *p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// Rank of entry me among the entries [b, e) of its class, four at a time
-// (the staging array has three spare entries past its end; entries past the
-// class never count).
-__device__ __forceinline__ uint32_t rank_in_class(const uint64_t *e64, uint32_t b, uint32_t e,
-                                                  uint64_t me) {
-  uint32_t rank = 0;
-  for (uint32_t y = b; y < e; y += 4) {
-    uint64_t m[4];
-#pragma unroll
-    for (int t = 0; t < 4; t++) m[t] = e64[y + t];
-#pragma unroll
-    for (int t = 0; t < 4; t++) rank += (uint32_t)((y + t < e) & (m[t] < me));
-  }
-  return rank;
 }
 
 // Switch ports, one level (App. B.3 switch constraints): a switched send
@@ -159,7 +144,7 @@ __device__ uint32_t ports_level(const PathArgs &a, int L, const uint32_t *gpr, u
     const int k = ecls2[x];
     const uint32_t cx = (uint32_t)e64[x] & 0xFFFFu;
     const uint32_t b = ccnt2[k];
-    sorted2[b + rank_in_class(e64, b, ccnt2[k + 1], e64[x])] = (uint16_t)cx;
+    sorted2[b + rank_in_bucket(e64, b, ccnt2[k + 1], e64[x])] = (uint16_t)cx;
     dl[cx] = a.cls2_link[lo2 + k];
   }
   __syncthreads();
@@ -353,7 +338,7 @@ __global__ __launch_bounds__(NT) void path_eval_kernel(PathArgs a) {
       for (uint32_t x = tid; x < tot; x += nt) {
         const int k = ecls[x];
         const uint32_t b = ccnt[k];
-        sorted[b + rank_in_class(e64, b, ccnt[k + 1], e64[x])] = (uint16_t)e64[x];
+        sorted[b + rank_in_bucket(e64, b, ccnt[k + 1], e64[x])] = (uint16_t)e64[x];
       }
       __syncthreads();
       if (a.ports) {
@@ -454,6 +439,11 @@ int32_t path_layout(const taccl_plan &p, PathArgs &a) {
   return off;
 }
 
+bool path_ports_supported(const taccl_plan &p, int max_lds) {
+  PathArgs a{};
+  return path_layout(p, a) <= max_lds && p.topo.E <= 4 * a.lr_threads;
+}
+
 hipError_t launch_path(const PathArgs &a, int grid, hipStream_t stream) {
   // switch-port plans whose levels hold more sends than four per thread of
   // a 256-thread block run 1024-thread blocks (the port passes keep four
@@ -495,57 +485,6 @@ namespace taccl {
 namespace {
 
 constexpr uint32_t kUnset = 0xFFFFFFFFu;
-
-// The top `bits` bits of x (0 for bits = 0): one bit-field extract, whose
-// width 0 gives 0
-__device__ __forceinline__ uint32_t top_bits(uint32_t x, uint32_t bits) {
-  return __builtin_amdgcn_ubfe(x, 32u - bits, bits);
-}
-
-// Exclusive scan of cnt[0..n) in place with cnt[n] = total (all threads
-// call; cnt 16-byte aligned; cnt[n+1..n+3] are overwritten as well). Each
-// wavefront takes a contiguous range of 4-word groups and each lane one
-// group per round, so a round reads 1 KB of consecutive words: one pass
-// for the wavefront totals, one to write the prefixes.
-__device__ void block_excl_scan4(uint32_t *cnt, int n, uint32_t *wsum) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
-  const int ng = (n >> 2) + 1;  // groups up to and including index n
-  const int gpw = ((ng + nw - 1) / nw + 63) & ~63;
-  const int g0 = wave * gpw;
-  uint4 *c4 = (uint4 *)cnt;
-  auto group = [&](int g) {  // entries from index n on count as 0
-    uint4 x = g < ng ? c4[g] : make_uint4(0u, 0u, 0u, 0u);
-    const int e = 4 * g;
-    x.x = e < n ? x.x : 0u;
-    x.y = e + 1 < n ? x.y : 0u;
-    x.z = e + 2 < n ? x.z : 0u;
-    x.w = e + 3 < n ? x.w : 0u;
-    return x;
-  };
-  uint32_t sum = 0;
-  for (int r = 0; r < gpw; r += 64) {
-    const uint4 x = group(g0 + r + lane);
-    sum += x.x + x.y + x.z + x.w;
-  }
-  const uint32_t wt = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add(sum), 63);
-  if (lane == 0) wsum[wave] = wt;
-  __syncthreads();
-  const uint32_t ws = row_scan_add(lane < nw ? wsum[lane] : 0u);
-  const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane(wave);
-  uint32_t run = w ? (uint32_t)__builtin_amdgcn_readlane((int)ws, w - 1) : 0u;
-  for (int r = 0; r < gpw; r += 64) {
-    const int g = g0 + r + lane;
-    const uint4 x = group(g);
-    const uint32_t gs = x.x + x.y + x.z + x.w;
-    const uint32_t inc = wave_scan_add(gs);
-    const uint32_t e0 = run + inc - gs;
-    // the group holding index n receives the total there (later entries
-    // count as 0)
-    if (g < ng) c4[g] = make_uint4(e0, e0 + x.x, e0 + x.x + x.y, e0 + x.x + x.y + x.z);
-    run += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-  }
-  __syncthreads();
-}
 
 template <int CPT, int NT, bool kContig>
 __global__ __launch_bounds__(NT) void path_eval_fast(PathArgs a) {

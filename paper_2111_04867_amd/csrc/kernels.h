@@ -112,6 +112,23 @@ struct PathArgs {
   int32_t lr_threads;  // block size of the LDS-record kernel for this plan
 };
 
+// Alltoall with switch ports, plans within the switch-port kernel's limits:
+// one block per candidate at a time.
+struct PortsArgs {
+  int32_t C, H, nlev, route_stride, prio_stride, routes_words;
+  int32_t nt, cpt, nports, nswitched, nrecv, nb1, nb2, ncls, ncls2, cbits;
+  const uint32_t *cost, *arec, *cpath, *cinfo, *cbkt, *lfb, *pwalk;
+  const uint16_t *pport;
+  const uint8_t *routes;
+  const uint32_t *prio;
+  uint32_t *makespan;
+  uint8_t *valid;
+  int64_t n;
+  // LDS carve-up
+  int32_t o_cinfo, o_cbkt, o_lfb, o_bst, o_e64, o_aux, o_pinfo, o_rk, o_red;
+  int32_t lds_bytes;
+};
+
 // Time-aware greedy orders for Alltoall: persistent blocks of wavefronts,
 // one candidate per wavefront at a time (send slots c*H + h).
 struct PathGreedyArgs {
@@ -217,6 +234,15 @@ int32_t path_fast_layout(const taccl_plan &p, PathArgs &a);
 int path_fast_cpt(const taccl_plan &p);      // chunks per thread, 0 = not eligible
 int path_fast_threads(const taccl_plan &p);  // threads per block: 256, 512 or 1024
 int path_fast_blocks_per_cu(const PathArgs &a, int cpt, int nt);
+
+// a switch-port plan is within what the general kernel takes (the plans that
+// evaluation accepts, whichever kernel runs them)
+bool path_ports_supported(const taccl_plan &p, int max_lds);
+// Alltoall with switch ports: fills the layout and returns the block's LDS
+// bytes, or 0 when the plan does not meet the kernel's conditions
+int32_t path_ports_layout(const taccl_plan &p, PortsArgs &a);
+int path_ports_blocks_per_cu(const PortsArgs &a);
+hipError_t launch_path_ports(const PortsArgs &a, int grid, hipStream_t stream);
 
 hipError_t launch_tree(const TreeArgs &a, int grid, hipStream_t stream);
 // Alltoall greedy: fills the layout; returns the bytes of a one-wavefront

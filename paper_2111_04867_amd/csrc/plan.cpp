@@ -474,6 +474,51 @@ static taccl_status_t build_levels(taccl_plan *p) {
     p->gk_count = (int32_t)uniq.size();
   }
 
+  const int32_t C = p->coll.C, cpr = p->coll.cpr;
+  auto chunk_table = [&]() {
+    p->cpath.assign(C, 0);
+    for (int32_t ch = 0; ch < C; ch++) {
+      const int32_t pair = ch / cpr, s = pair / P, d = pair % P;
+      if (s == d) continue;
+      const size_t pp = (size_t)s * P + d;
+      // a pair without any route option can never be delivered: marked by
+      // an all-ones option index and no options
+      p->cpath[ch] = p->npaths[pp] ? (p->pair_base[pp] + 1) | ((uint32_t)p->npaths[pp] << 24)
+                                   : kNoRoute;
+    }
+  };
+  // bits of priority sub-buckets per class: log2 of the class's expected
+  // membership under uniform route choice (classes of each hop in `cls`)
+  auto class_bits = [&](const std::vector<uint16_t> &cls, int32_t n) {
+    std::vector<double> expect(n, 0.0);
+    for (int32_t s2 = 0; s2 < P; s2++)
+      for (int32_t d2 = 0; d2 < P; d2++) {
+        if (s2 == d2) continue;
+        const size_t pp = (size_t)s2 * P + d2;
+        const int32_t np = p->npaths[pp];
+        for (int32_t k = 0; k < np; k++) {
+          const uint32_t q = p->pair_base[pp] + k;
+          for (uint32_t j = p->path_off[q]; j < p->path_off[q + 1]; j++)
+            if (cls[j] != 0xFFFF) expect[cls[j]] += (double)cpr / np;
+        }
+      }
+    std::vector<int> bits(n, 0);
+    for (int32_t k = 0; k < n; k++)
+      while (bits[k] < 10 && (double)(2u << bits[k]) <= expect[k]) bits[k]++;
+    return bits;
+  };
+  // appends first bucket | bits << 24 of every class to `out` and returns the
+  // next bucket. Classes are numbered level by level, so one running count
+  // numbers every level's buckets in level order
+  auto number_buckets = [](const std::vector<int> &bits, uint64_t nb, std::vector<uint32_t> &out) {
+    out.clear();
+    for (int b : bits) {
+      out.push_back((uint32_t)nb | ((uint32_t)b << 24));
+      nb += 1u << b;
+    }
+    return nb;
+  };
+
   // compact tables of the register-resident kernel (paths of <= 6 hops,
   // <= 8 levels, fewer than 2^24 - 2 route options)
   p->path_fast = !p->ports && p->H <= kFastMaxHops && p->nlev <= 8 && npath + 1 < kNoRoute &&
@@ -497,46 +542,15 @@ static taccl_status_t build_levels(taccl_plan *p) {
       }
       r[0] = (uint32_t)h | (hm << 8);
     }
-    const int32_t C = p->coll.C, cpr = p->coll.cpr;
-    p->cpath.assign(C, 0);
-    for (int32_t ch = 0; ch < C; ch++) {
-      const int32_t pair = ch / cpr, s = pair / P, d = pair % P;
-      if (s == d) continue;
-      const size_t pp = (size_t)s * P + d;
-      // a pair without any route option can never be delivered: marked by
-      // an all-ones option index and no options
-      p->cpath[ch] = p->npaths[pp] ? (p->pair_base[pp] + 1) | ((uint32_t)p->npaths[pp] << 24)
-                                   : kNoRoute;
-    }
+    chunk_table();
     // priority sub-buckets per class, sized from the class's expected
     // membership under uniform route choice so a bucket holds 1-2 sends
     // (any input stays exact: a crowded bucket is only slower to order),
     // then halved all over until every level's buckets together fit the
     // kernel's counters
-    std::vector<double> expect(p->ncls, 0.0);
-    for (int32_t s2 = 0; s2 < P; s2++)
-      for (int32_t d2 = 0; d2 < P; d2++) {
-        if (s2 == d2) continue;
-        const size_t pp = (size_t)s2 * P + d2;
-        const int32_t np = p->npaths[pp];
-        for (int32_t k = 0; k < np; k++) {
-          const uint32_t q = p->pair_base[pp] + k;
-          for (uint32_t j = p->path_off[q]; j < p->path_off[q + 1]; j++)
-            expect[p->hop_class[j]] += (double)cpr / np;
-        }
-      }
-    std::vector<int> cbits(p->ncls, 0);
-    for (int32_t k = 0; k < p->ncls; k++)
-      while (cbits[k] < 10 && (double)(2u << cbits[k]) <= expect[k]) cbits[k]++;
-    p->cbkt.assign(p->ncls, 0);
+    std::vector<int> cbits = class_bits(p->hop_class, p->ncls);
     for (;;) {
-      // classes are numbered level by level, so one running count numbers
-      // every level's buckets in level order
-      uint64_t nb = 0;
-      for (int32_t k = 0; k < p->ncls; k++) {
-        p->cbkt[k] = (uint32_t)nb | ((uint32_t)cbits[k] << 24);
-        nb += 1u << cbits[k];
-      }
+      const uint64_t nb = number_buckets(cbits, 0, p->cbkt);
       p->nb_total = (int32_t)std::min<uint64_t>(nb, INT32_MAX);
       if (nb <= (uint64_t)kFastMaxBuckets || p->ncls > kFastMaxBuckets) break;
       for (int &b : cbits) b = std::max(b - 1, 0);
@@ -548,6 +562,93 @@ static taccl_status_t build_levels(taccl_plan *p) {
         const uint32_t first = p->llc[((size_t)L * E + l) * 2];
         p->cinfo[k] = l | ((p->cbkt[first] & 0xFFFFFFu) << 16);
       }
+  }
+
+  // tables of the switch-port kernel, under the same limits: classes and
+  // buckets of both port orders, numbered in one sequence (send ports, one
+  // bucket that stays empty, receive ports: a bucket's start is where the
+  // one before it ends, and the receive ports' first bucket must not wait
+  // for the last level's send ports)
+  const int32_t ncls2 = (int32_t)p->cls2_link.size();
+  p->ports_fast = p->ports && p->H <= kFastMaxHops && p->nlev <= 8 && npath + 1 < kNoRoute &&
+                  C <= kFastMaxChunks && p->ncls + ncls2 + 1 <= kPortsMaxBuckets;
+  if (p->ports_fast) {
+    // per route option 8 words: hop at each level (3 bits, 7: none), send-port
+    // classes, one spare, receive-port classes (0xFFFF: no send starts there);
+    // record 0 has none
+    p->arec.assign((npath + 1) * 8, 0xFFFFFFFFu);
+    for (size_t q = 0; q < npath; q++) {
+      uint32_t *r = &p->arec[(q + 1) * 8];
+      uint64_t rem = ucost[q];
+      for (const Unit &x : units[q]) {
+        const uint32_t lv = (uint32_t)level_of(rem), j = p->path_off[q] + x.j, sh = 16 * (x.j & 1);
+        r[0] = (r[0] & ~(7u << (3 * lv))) | (x.j << (3 * lv));
+        r[1 + x.j / 2] &= ~(0xFFFFu << sh) | ((uint32_t)p->hop_class[j] << sh);
+        r[4 + x.j / 2] &= ~(0xFFFFu << sh) | ((uint32_t)p->hop_class2[j] << sh);
+        rem -= x.cost;
+      }
+    }
+    chunk_table();
+    std::vector<int> bits = class_bits(p->hop_class, p->ncls);
+    std::vector<int> bits2 = class_bits(p->hop_class2, ncls2);
+    std::vector<uint32_t> bk, bk2;
+    uint64_t nb = 0;
+    for (;;) {
+      const uint64_t n1 = number_buckets(bits, 0, bk) + 1;
+      nb = number_buckets(bits2, n1, bk2);
+      p->nb_total = (int32_t)n1;
+      p->nb2_total = (int32_t)(nb - n1);
+      if (nb <= (uint64_t)kPortsMaxBuckets) break;
+      for (int &b : bits) b = std::max(b - 1, 0);
+      for (int &b : bits2) b = std::max(b - 1, 0);
+    }
+    auto bucket = [&](const std::vector<uint32_t> &b, uint32_t k, uint32_t end) {
+      return k < b.size() ? b[k] & 0xFFFFFFu : end;
+    };
+    const uint32_t end1 = (uint32_t)p->nb_total - 1, end2 = (uint32_t)nb;
+    p->ports_lfb.clear();
+    for (int32_t L = 0; L <= p->nlev; L++)
+      p->ports_lfb.push_back(bucket(bk, p->lvl_cls_begin[L], end1));
+    for (int32_t L = 0; L <= p->nlev; L++)
+      p->ports_lfb.push_back(bucket(bk2, p->lvl_cls2_begin[L], end2));
+    p->cinfo.assign(ncls2, 0);
+    std::vector<int32_t> recv((size_t)E, -1);  // receive ports, numbered
+    p->nrecv = 0;
+    std::vector<uint8_t> sends((size_t)E, 0);
+    for (int32_t L = 0; L < p->nlev; L++)
+      for (int32_t l = 0; l < E; l++) {
+        const uint32_t *c1 = &p->llc[((size_t)L * E + l) * 2];
+        const uint32_t *c2 = &p->llc2[((size_t)L * E + l) * 2];
+        sends[l] |= c1[0] != c1[1];
+        if (c2[0] != c2[1] && recv[l] < 0) recv[l] = p->nrecv++;
+        for (uint32_t k = c2[0]; k < c2[1]; k++)
+          p->cinfo[k] = (uint32_t)recv[l] | (bucket(bk2, c2[0], end2) << 16);
+      }
+    // send ports, one per thread: those into one switch side by side, and in
+    // one wavefront where they fit (0xFFFF fills up), then, from a wavefront
+    // of their own on, the plain links
+    std::vector<std::vector<uint16_t>> into((size_t)p->topo.V + 1);
+    for (int32_t l = 0; l < E; l++)
+      if (sends[l]) into[p->ldst[l] >= P ? p->ldst[l] : p->topo.V].push_back((uint16_t)l);
+    p->pport.clear();
+    for (int32_t v = P; v <= p->topo.V; v++) {
+      const size_t room = (64 - p->pport.size() % 64) % 64, n = into[v].size();
+      if (v == p->topo.V) p->nswitched = (int32_t)p->pport.size();
+      if ((v == p->topo.V && n) || (n > room && n <= 64)) p->pport.resize(p->pport.size() + room, 0xFFFF);
+      p->pport.insert(p->pport.end(), into[v].begin(), into[v].end());
+    }
+    // per level and port: first bucket | end bucket << 16 of its run (0: none)
+    const size_t np = p->pport.size();
+    p->pwalk.assign(np * std::max(p->nlev, 1), 0);
+    for (int32_t L = 0; L < p->nlev; L++)
+      for (size_t t = 0; t < np; t++) {
+        if (p->pport[t] == 0xFFFF) continue;
+        const uint32_t *c1 = &p->llc[((size_t)L * E + p->pport[t]) * 2];
+        if (c1[0] != c1[1])
+          p->pwalk[L * np + t] = bucket(bk, c1[0], end1) | (bucket(bk, c1[1], end1) << 16);
+      }
+    p->cbkt = bk;
+    p->cbkt.insert(p->cbkt.end(), bk2.begin(), bk2.end());
   }
   return TACCL_OK;
 }
@@ -1010,7 +1111,11 @@ taccl_status_t taccl_sketch_apply(taccl_topology_t topo, taccl_collective_t coll
   if (coll->kind == TACCL_ALLTOALL) {
     PathArgs a{};
     PathGreedyArgs g{};
-    if (p->greedy)
+    PortsArgs t{};
+    const int32_t ports = path_ports_layout(*p, t);
+    if (ports > 0 && ports <= kLdsBytes && path_ports_supported(*p, kLdsBytes))
+      p->path_lds = ports;
+    else if (p->greedy)
       p->path_lds = path_greedy_layout(*p, g) > 0 ? g.o_wave + g.wave_bytes
                                                   : path_greedy_block_layout(*p, g);
     else

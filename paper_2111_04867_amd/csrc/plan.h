@@ -17,6 +17,10 @@ constexpr int kFastMaxChunks = 4096;
 // priority sub-buckets of all levels together in the register-resident
 // Alltoall kernel (one LDS counter each)
 constexpr int kFastMaxBuckets = 16384;
+// the same for the switch-port kernel (both port orders' buckets together)
+constexpr int kPortsMaxBuckets = 12288;
+// LDS of a CU, and of the largest block
+constexpr int32_t kLdsBytes = 160 * 1024;
 // chunk table entry of a pair that has no route option at all
 constexpr uint32_t kNoRoute = 0x00FFFFFFu;
 
@@ -49,7 +53,7 @@ struct LaunchShape {
 // the kernels a plan may launch, each with a shape of its own
 enum ShapeOf { kShapeTree, kShapeTreeReduce, kShapeLayers, kShapeLayersReduce, kShapeRank,
                kShapeRankReduce, kShapePathGreedy, kShapePathGreedyBlock, kShapePathFast,
-               kNumShapes };
+               kShapePathPorts,               kNumShapes };
 
 // Device copies of the read-only plan tables (one set per device).
 struct DeviceTables {
@@ -79,6 +83,8 @@ struct DeviceTables {
   const uint32_t *llc = nullptr;
   const uint32_t *arec = nullptr, *cpath = nullptr, *cinfo = nullptr, *cbkt = nullptr;
   const uint32_t *gkrank = nullptr;
+  const uint32_t *ports_lfb = nullptr, *pwalk = nullptr;
+  const uint16_t *pport = nullptr;
   const uint32_t *cn_rec = nullptr, *cn_chunk = nullptr;
   // Depends on the plan and the device alone, so it is worked out on first
   // use and kept (under the plan's mutex): the runtime's occupancy query for
@@ -175,6 +181,17 @@ struct taccl_plan {
   // them.
   std::vector<uint32_t> cbkt;
   int32_t nb_total = 0;
+  // switch-port kernel: arec holds 8 words per option (receive-port classes
+  // too), cbkt the receive-port classes after the send-port ones, cinfo the
+  // receive-port classes alone,
+  // nb_total and nb2_total the buckets of the two orders; per order the
+  // first bucket of every level, the send ports by thread, and the first and
+  // end bucket of every level's run on them
+  bool ports_fast = false;
+  int32_t nb2_total = 0;
+  int32_t nswitched = 0, nrecv = 0;  // threads up to the last switched send port; receive ports
+  std::vector<uint32_t> ports_lfb, pwalk;
+  std::vector<uint16_t> pport;
   // Alltoall greedy orders: per hop (index into path_links) the rank of its
   // Step-2 key (remaining desc, travelled asc) among all hops of the plan,
   // with the lengths of the greedy's direction (mirrored in reverse path

@@ -141,3 +141,44 @@ def test_large_levels(P, cpr, relays):
     plan, ref, opts = plans(w)
     routes, prio = generate(70 + P, 0, 24, opts, plan.prio_stride)
     check(plan, ref, routes, prio, f"{w.name} cpr={cpr}")
+
+
+def switch_and_ring(P, cpr):
+    """A switch next to a ring of direct links: plain and switched sends of
+    one level, in different wavefronts."""
+    edges = cf.switch_edges(range(P), P, 700, 8) + cf.ring_edges(range(P), 500, 30)
+    row_ptr, col, a, b = cf.csr_from_edges(P + 1, edges)
+    return cf.Workload(f"switchring{P}", P + 1, P, row_ptr, col, a, b, None, cf.ALLTOALL, cpr,
+                       65536, cf.KSHORTEST, k=3, switch_ports=1)
+
+
+# every block size and chunks per thread, and the first plan past them
+@pytest.mark.parametrize("P,cpr,n", [(1, 1, 3), (16, 1, 300), (17, 1, 300), (22, 1, 130),
+                                     (23, 1, 65), (32, 1, 40), (33, 1, 40), (45, 1, 20),
+                                     (46, 1, 20), (64, 1, 12), (46, 2, 6)])
+def test_block_sizes(P, cpr, n):
+    for w in (star(P, relays=P < 33, cpr=cpr), switch_and_ring(P, cpr) if 2 < P < 33 else None):
+        if w is None:
+            continue
+        plan, ref, opts = plans(w)
+        routes, prio = generate(80 + P, 0, n, opts, plan.prio_stride)
+        rng = np.random.default_rng(P)
+        routes[rng.random(routes.shape) < 0.02] = 0xFF  # unrouted pairs
+        prio[rng.random(prio.shape) < 0.3] &= 1         # equal priorities
+        check(plan, ref, routes, prio, f"{w.name} cpr={cpr}")
+
+
+def test_unaligned_routes():
+    """Route rows of whole words behind a pointer that is not word aligned."""
+    w = star(16, True, 1)
+    plan, ref, opts = plans(w)
+    routes, prio = generate(5, 0, 70, opts, plan.prio_stride)
+    buf = torch.zeros(routes.size + 1, dtype=torch.uint8, device="cuda")
+    buf[1:] = torch.from_numpy(routes.reshape(-1))
+    mk = torch.empty(70, dtype=torch.int32, device="cuda")
+    ok = torch.empty(70, dtype=torch.uint8, device="cuda")
+    plan.eval_tensors(buf[1:].view(70, -1), torch.from_numpy(prio.view(np.int32)).cuda(), mk, ok)
+    torch.cuda.synchronize()
+    rmk, rok = ref.eval(routes, prio)
+    assert np.array_equal(mk.cpu().numpy().view(np.uint32), rmk)
+    assert np.array_equal(ok.cpu().numpy(), rok)
