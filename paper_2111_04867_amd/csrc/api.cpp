@@ -301,7 +301,7 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
       const int nt = path_fast_threads(*p);
       const LaunchShape sh = launch_shape(
           p, t, kShapePathFast, 1, [&](int) { return a.lds_bytes; },
-          [&](int) { return std::min(4, path_fast_blocks_per_cu(a, cpt, nt)); });
+          [&](int) { return path_fast_blocks_per_cu(a, cpt, nt); });
       const int fgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
       e = launch_path_fast(a, cpt, nt, fgrid, s);
     } else {
