@@ -54,7 +54,8 @@ taccl_status_t ensure_device(taccl_plan *p, DeviceTables **out) {
          o_lcb2 = pk.add(p->lvl_cls2_begin), o_llc2 = pk.add(p->llc2),
          o_gkr = pk.add(p->gkrank), o_rimg = pk.add(p->rank_img), o_tent = pk.add(p->tent), o_c2l = pk.add(p->cls2_link),
          o_cnr = pk.add(p->cn_rec), o_cnc = pk.add(p->cn_chunk),
-         o_plfb = pk.add(p->ports_lfb), o_pwalk = pk.add(p->pwalk), o_pport = pk.add(p->pport);
+         o_plfb = pk.add(p->ports_lfb), o_pwalk = pk.add(p->pwalk), o_pport = pk.add(p->pport),
+         o_cml = pk.add(p->cml), o_cwalk = pk.add(p->cwalk);
   void *blk = nullptr;
   e = hipMalloc(&blk, pk.bytes.size());
   if (e != hipSuccess) return fail(TACCL_ERR_NO_MEMORY, "hipMalloc of plan tables failed");
@@ -101,6 +102,8 @@ taccl_status_t ensure_device(taccl_plan *p, DeviceTables **out) {
   t.ports_lfb = (const uint32_t *)at(o_plfb);
   t.pwalk = (const uint32_t *)at(o_pwalk);
   t.pport = (const uint16_t *)at(o_pport);
+  t.cml = (const uint32_t *)at(o_cml);
+  t.cwalk = (const uint32_t *)at(o_cwalk);
   t.cn_rec = p->cn_rec.empty() ? nullptr : (const uint32_t *)at(o_cnr);
   t.cn_chunk = (const uint32_t *)at(o_cnc);
   t.max_lds = (int)prop.sharedMemPerBlock;
@@ -286,6 +289,9 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     a.lalpha = t->lalpha;
     a.lbs = t->lbs;
     a.lmerge = t->lmerge;
+    a.cml = (const uint4 *)t->cml;
+    a.cwalk = t->cwalk;
+    a.nmerge = (int32_t)p->cml.size() / 4;
     a.ports = p->ports;
     a.hop_class2 = t->hop_class2;
     a.lvl_cls2_begin = t->lvl_cls2_begin;

@@ -628,6 +628,73 @@ __global__ __launch_bounds__(NT) void path_eval_fast(PathArgs a) {
     block_excl_scan4(bst + 1, (int)NBT, red);
 
     uint32_t mk = 0;
+    // Contiguous transfers: the level's runs on links between nodes, one
+    // wavefront per run at a time. Every send of a level has the same
+    // remaining length, so a send joins the open transfer when its chunk was
+    // ready at its start: with one ready time per lane, a ballot gives all the
+    // joiners of a transfer at once, and a run takes a step per transfer (a
+    // lane walking its run send by send, two dependent LDS reads and a 64-bit
+    // division each: fournode64, 8192 candidates, 2.69 ms; 1.75 ms so).
+    auto merged_runs = [&](int L, uint32_t lb0, auto div_e, uint32_t ep) {
+      auto at = [&](uint32_t y) -> uint32_t {  // packed send at sorted position y
+        const uint32_t ty = div_e(y);
+        return pinfo[(y - __umul24(ty, ep)) * NT + ty];
+      };
+      for (int g = 0; g < a.nmerge; g += NT) {
+        // 64 links per wavefront, one per lane: bounds, latency and size term
+        const int k = g + lane * (NT / 64) + wave;
+        uint32_t be = 0, ml = 0, al0 = 0, bs_lo = 0, bs_hi = 0, xb0 = 0, xe0 = 0;
+        if (k < a.nmerge) {
+          be = a.cwalk[(size_t)L * a.nmerge + k];
+          const uint4 m = a.cml[k];
+          ml = m.x;
+          al0 = m.y;
+          bs_lo = m.z;
+          bs_hi = m.w;
+        }
+        if (be) {
+          xb0 = bst[be & 0xFFFFu] - lb0;
+          xe0 = bst[be >> 16] - lb0;
+        }
+        for (uint64_t todo = __ballot(xe0 > xb0); todo; todo &= todo - 1) {
+          const int t = __builtin_ctzll(todo);
+          auto of = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, t); };
+          const uint32_t xb = of(xb0), xe = of(xe0), l = of(ml), al = of(al0);
+          const uint64_t bsz = ((uint64_t)of(bs_hi) << 32) | of(bs_lo);
+          uint32_t F = (uint32_t)__builtin_amdgcn_readfirstlane((int)lfc[l].x);
+          // chunks and ready times of positions wb .. wb + 63 (past the run:
+          // never ready)
+          uint32_t wb = xb, r = 0, ch = 0;
+          auto window = [&](uint32_t b) {
+            wb = b;
+            const uint32_t y = b + (uint32_t)lane;
+            ch = y < xe ? at(y) & cmask : 0u;
+            r = y < xe ? ctime[ch] : 0xFFFFFFFFu;
+          };
+          window(xb);
+          for (uint32_t i = xb; i < xe;) {
+            if (i - wb >= 64) window(i);
+            const uint32_t gs =
+                max(F, (uint32_t)__builtin_amdgcn_readlane((int)r, (int)(i - wb)));
+            uint32_t j = i;  // end of the transfer that position i opens
+            for (;;) {
+              const uint64_t stop = ~(__ballot(r <= gs) >> (j - wb));
+              j += stop ? (uint32_t)__builtin_ctzll(stop) : 64u;
+              if (j - wb < 64 || j >= xe) break;
+              window(j);
+            }
+            const uint32_t f = gs + al + (uint32_t)((bsz * (j - i) + 999) / 1000);
+            // its sends in this window, and those in windows before it
+            if (wb + (uint32_t)lane >= i && wb + (uint32_t)lane < j) ctime[ch] = f;
+            for (uint32_t y = i + (uint32_t)lane; y < wb; y += 64) ctime[at(y) & cmask] = f;
+            F = f;
+            i = j;
+          }
+          mk = max(mk, F);
+          if (lane == 0) lnext[l] = F;
+        }
+      }
+    };
     for (int L = 0; L < nlev; L++) {
       // this level's first position among all levels' sends (the end of the
       // previous level's last bucket, untouched during this level)
@@ -680,33 +747,21 @@ __global__ __launch_bounds__(NT) void path_eval_fast(PathArgs a) {
       __syncthreads();
       const uint32_t tot = bst[s_lfb[L + 1]] - lb0;
       const uint32_t ept = (tot + NT - 1) / NT;  // <= CPT: a level has <= C sends
-      // pos / ept for pos < 2^16 and ept <= 4 (the same for every thread):
-      // a shift, or (pos * 43691) >> 17 for 3 (exact below 2^17); 24-bit
-      // multiplies issue at the full VALU rate
-      const uint32_t esh = ept >= 4 ? 2u : ept >= 2 ? 1u : 0u;
-      auto div_ept = [&](uint32_t pos) -> uint32_t {
-        return ept == 3 ? __umul24(pos, 43691u) >> 17 : pos >> esh;
-      };
-      // the contiguity walker divides with one 64-bit multiply
-      // (y / ept = (y * em) >> 32, em = floor((2^32 - 1) / ept) + 1)
-      const uint64_t em = (kContig && ept) ? 0xFFFFFFFFull / ept + 1 : 0;
-      // The level's ordering and timing passes. Without contiguity the
-      // level's ept (the same for every thread) is a compile-time constant
-      // EP in each copy of them below; with it, one copy takes EP = CPT and
-      // the level's ept at run time (keeping the run walker in one copy).
+      // The level's ordering and timing passes: the level's ept (the same for
+      // every thread) is a compile-time constant EP in each copy of them below
       auto order_and_time = [&](auto ep_c) {
       constexpr int EP = decltype(ep_c)::value;
-      const uint32_t epr = kContig ? ept : (uint32_t)EP;
+      constexpr uint32_t epr = (uint32_t)EP;
       // ---- D. order inside buckets by (priority, chunk); record each send's
       //      link and its index in the link's run -------------------------
       // One lane per bucket-sorted position: neighbouring lanes hold
       // neighbouring buckets, so their members are read with few bank
       // conflicts, and a pass waits only for the largest bucket among its
       // 64 positions.
+      // pos / EP for pos < 2^16: a shift, or (pos * 43691) >> 17 for 3 (exact
+      // below 2^17; 24-bit multiplies issue at the full VALU rate)
       auto div_e = [&](uint32_t pos) -> uint32_t {
-        if constexpr (kContig)
-          return div_ept(pos);
-        else if constexpr (EP == 3)
+        if constexpr (EP == 3)
           return __umul24(pos, 43691u) >> 17;
         else
           return pos >> (EP == 4 ? 2 : EP == 2 ? 1 : 0);
@@ -734,6 +789,7 @@ __global__ __launch_bounds__(NT) void path_eval_fast(PathArgs a) {
         pinfo[q * NT + t] = (uint32_t)me | ((pos - rs) << kb);
       }
       __syncthreads();
+      if constexpr (kContig) merged_runs(L, lb0, div_e, epr);
       // ---- E. finish times of every link run --------------------------------
       // The k-th send of a link run with cost c, ready times r_j and busy
       // time F finishes at (k+1)c + max_{j<=k} a_j with a_0 = max(r_0, F)
@@ -824,42 +880,7 @@ __global__ __launch_bounds__(NT) void path_eval_fast(PathArgs a) {
         const uint32_t x = x0 + q;
         if ((uint32_t)q < epr && x < tot) {
           const uint32_t c = pis[q] & cmask, l = (pis[q] >> cb) & lmask, k = pis[q] >> kb;
-          if (kContig && s_merge[l]) {
-            // contiguous transfers: the run's first position walks the run
-            // (every send of a level has the same remaining length); a send
-            // joins the open transfer when its chunk was ready at its start
-            if (k == 0) {
-              const uint32_t al = a.lalpha[l];
-              const uint64_t bsz = a.lbs[l];
-              uint32_t F = lf[q], gs = 0, gm = 0, g0 = x;
-              auto at = [&](uint32_t y) {  // packed send at sorted position y
-                const uint32_t ty = (uint32_t)(((uint64_t)y * em) >> 32);
-                return pinfo[(y - ty * ept) * NT + ty];
-              };
-              for (uint32_t y = x;; y++) {
-                const uint32_t py = (y < tot) ? at(y) : 0u;
-                const bool end = y == tot || (y > x && (py >> kb) == 0);
-                const uint32_t ry = end ? 0u : ctime[py & cmask];
-                const bool join = !end && gm > 0 && ry <= gs;
-                if (gm > 0 && !join) {  // close the open transfer
-                  const uint32_t f = gs + al + (uint32_t)((bsz * gm + 999) / 1000);
-                  for (uint32_t t = g0; t < g0 + gm; t++) ctime[at(t) & cmask] = f;
-                  F = f;
-                  mk = max(mk, f);
-                }
-                if (end) break;
-                if (join) {
-                  gm++;
-                } else {
-                  gs = max(F, ry);
-                  gm = 1;
-                  g0 = y;
-                }
-              }
-              lnext[l] = F;
-            }
-            continue;
-          }
+          if (kContig && s_merge[l]) continue;  // timed by merged_runs
           const uint32_t cl = cs[q];
           // the run began before this thread's first position: k > q
           const uint32_t best = k > (uint32_t)q ? max(sv[q], cin) : sv[q];
@@ -871,9 +892,7 @@ __global__ __launch_bounds__(NT) void path_eval_fast(PathArgs a) {
         }
       }
       };
-      if constexpr (kContig) {
-        order_and_time(std::integral_constant<int, CPT>{});
-      } else if (ept <= 1) {
+      if (ept <= 1) {
         order_and_time(std::integral_constant<int, 1>{});
       } else if constexpr (CPT >= 2) {
         if (ept == 2) {

@@ -104,6 +104,11 @@ struct PathArgs {
   const uint64_t *lbs;    // beta * chunk_bytes per link
   const uint8_t *lmerge;  // 1: the link joins two nodes
   int32_t o_fmerge;
+  // the links that merge ({link, alpha, beta * chunk_bytes lo, hi}), and per
+  // level the first and end bucket of their runs (0: none)
+  const uint4 *cml;
+  const uint32_t *cwalk;
+  int32_t nmerge;
   // switch ports (LDS-record kernel): receive-port classes and state
   int32_t ports;
   const uint16_t *hop_class2, *cls2_link;

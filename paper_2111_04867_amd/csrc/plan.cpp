@@ -562,6 +562,26 @@ static taccl_status_t build_levels(taccl_plan *p) {
         const uint32_t first = p->llc[((size_t)L * E + l) * 2];
         p->cinfo[k] = l | ((p->cbkt[first] & 0xFFFFFFu) << 16);
       }
+    p->cml.clear();
+    p->cwalk.clear();
+    if (p->contig && p->ncls <= kFastMaxBuckets) {
+      for (int32_t l = 0; l < E; l++) {
+        bool sends = false;
+        for (int32_t L = 0; L < p->nlev; L++)
+          sends |= p->llc[((size_t)L * E + l) * 2] != p->llc[((size_t)L * E + l) * 2 + 1];
+        if (sends && p->lmerge[l])
+          p->cml.insert(p->cml.end(), {(uint32_t)l, p->lalpha[l], (uint32_t)p->lbs[l],
+                                       (uint32_t)(p->lbs[l] >> 32)});
+      }
+      for (int32_t L = 0; L < p->nlev; L++)
+        for (size_t i = 0; i < p->cml.size(); i += 4) {
+          const uint32_t l = p->cml[i];
+          const uint32_t *c = &p->llc[((size_t)L * E + l) * 2];
+          const uint32_t end =
+              c[1] < p->cbkt.size() ? p->cbkt[c[1]] & 0xFFFFFFu : (uint32_t)p->nb_total;
+          p->cwalk.push_back(c[0] == c[1] ? 0u : (p->cbkt[c[0]] & 0xFFFFFFu) | (end << 16));
+        }
+    }
   }
 
   // tables of the switch-port kernel, under the same limits: classes and

@@ -85,6 +85,7 @@ struct DeviceTables {
   const uint32_t *gkrank = nullptr;
   const uint32_t *ports_lfb = nullptr, *pwalk = nullptr;
   const uint16_t *pport = nullptr;
+  const uint32_t *cml = nullptr, *cwalk = nullptr;
   const uint32_t *cn_rec = nullptr, *cn_chunk = nullptr;
   // Depends on the plan and the device alone, so it is worked out on first
   // use and kept (under the plan's mutex): the runtime's occupancy query for
@@ -180,6 +181,10 @@ struct taccl_plan {
   // over all levels at once (level by level, class by class), nb_total of
   // them.
   std::vector<uint32_t> cbkt;
+  // contiguity: the links that merge and carry sends (4 words each: link,
+  // alpha, beta * chunk_bytes), and per level and such link first bucket |
+  // end bucket << 16 of its run (0: none)
+  std::vector<uint32_t> cml, cwalk;
   int32_t nb_total = 0;
   // switch-port kernel: arec holds 8 words per option (receive-port classes
   // too), cbkt the receive-port classes after the send-port ones, cinfo the

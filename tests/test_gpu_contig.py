@@ -143,3 +143,44 @@ def test_large_plan_on_the_general_kernel():
     prio[:, ::3] = 9
     mk, ok = check(plan, ref, routes, prio, "uniring40 contig")
     assert ok.all()
+
+
+def two_switch_nodes(per, relays, alpha, cpr=1):
+    """Two switch machines joined by `relays` IB links each way, of latency
+    `alpha`: every link between them carries per * per * cpr / relays sends."""
+    P = 2 * per
+    edges = [e for n in range(2)
+             for e in cf.switch_edges(range(n * per, (n + 1) * per), P + n, 700, 8)]
+    for i in range(relays):
+        edges += [(i, per + i, alpha, 106), (per + i, i, alpha, 106)]
+    row_ptr, col, a, b = cf.csr_from_edges(P + 2, edges)
+    node_of = np.array([r // per for r in range(P)] + [0, 1], dtype=np.int32)
+    relay = np.zeros(P + 2, dtype=np.uint8)
+    for i in range(relays):
+        relay[[i, per + i]] = 1
+    return cf.Workload(f"twoswitch{per}r{relays}", P + 2, P, row_ptr, col, a, b, node_of,
+                       cf.ALLTOALL, cpr, 16384, cf.HIER_RELAY, max_cross=1, relay=relay,
+                       contiguity=1)
+
+
+# runs of one send to several times a wavefront, transfers of one send (an
+# idle link) to whole runs (a latency no queue outlasts), in blocks of every
+# size
+@pytest.mark.parametrize("per,relays,alpha,cpr", [(2, 1, 1700, 1), (8, 1, 1700, 1),
+                                                  (8, 1, 1, 4), (8, 2, 300000, 2),
+                                                  (11, 1, 40000, 1), (13, 1, 9000, 2),
+                                                  (16, 1, 300000, 1), (23, 4, 100000, 1)])
+def test_long_runs(per, relays, alpha, cpr):
+    from paper_2111_04867_amd.binding import Plan
+    w = two_switch_nodes(per, relays, alpha, cpr)
+    plan, ref = Plan.from_workload(w), OraclePlan.from_workload(w)
+    opts = plan.route_options()
+    assert (opts == ref.route_options()).all()
+    n = 40 if per < 16 else 12
+    routes, prio = generate(90 + per, 0, n, opts, plan.prio_stride)
+    rng = np.random.default_rng(per)
+    routes[rng.random(routes.shape) < 0.02] = 0xFF
+    prio[rng.random(prio.shape) < 0.3] &= 1
+    mk, ok = plan.eval(routes, prio)
+    rmk, rok = ref.eval(routes, prio)
+    assert np.array_equal(mk, rmk) and np.array_equal(ok, rok), w.name
