@@ -344,12 +344,12 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     a.makespan = d_makespan;
     a.valid = d_valid;
     a.n = n;
+    a.ent = t->tent;
     // the layered kernel needs whole route words and priorities in registers
     const bool greedy = p->greedy != 0;
-    const bool layered =
-        a.routes_word_aligned &&
-        (greedy ? tree_greedy_layout(*p, a) : tree_layers_layout(*p, a)) > 0 &&
-        tree_block_bytes(a, 1) <= t->max_lds;
+    const bool layered = (greedy ? tree_greedy_layout(*p, a) > 0
+                                 : a.routes_word_aligned && tree_layers_layout(*p, a) > 0) &&
+                         tree_block_bytes(a, 1) <= t->max_lds;
     const int kind = p->coll.kind;
     const bool reduction = kind == TACCL_REDUCESCATTER || kind == TACCL_ALLREDUCE;
     // plans outside the layered kernel's limits: the general kernel, whose
@@ -387,7 +387,6 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     const bool ranked = !greedy && t->rank_img &&
                         tree_rank_layout(*p, ra) > 0 && tree_block_bytes(ra, 1) <= t->max_lds;
     ra.rank_img = (const uint4 *)t->rank_img;
-    ra.ent = t->tent;
     const bool ranked_rs = ranked && p->rank_rs_ok;
     auto launch_ranked = [&](TreeArgs &x) {
       const LaunchShape sh = launch_shape(

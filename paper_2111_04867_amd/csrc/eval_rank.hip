@@ -76,9 +76,6 @@ constexpr int rank_max_threads() {
   return J <= 8 ? kRankMaxThreads : 512;
 }
 
-// Four route bytes from any byte address in one load
-typedef uint32_t __attribute__((aligned(1))) u32_any;
-
 // Route word j (route bytes of chunk j / PW, padded to PW words) as one-hot
 // option bytes:
 // 1 << choice, 0 for a choice of 8 or more (no pair of these plans has as
@@ -668,12 +665,6 @@ __global__ __launch_bounds__(rank_max_threads<J>()) void tree_rank_kernel(TreeAr
 
 int32_t align16(int32_t x) { return (x + 15) & ~15; }
 
-// Route words per chunk of the instantiation that runs P ranks
-int rank_words(int P) {
-  const int w = (P + 3) / 4;
-  return w == 5 ? 6 : w == 7 ? 8 : w;
-}
-
 // Slots per lane of the instantiation that runs C * V slots
 int rank_slots_per_lane(int cv) {
   const int j = (cv + 63) / 64;
@@ -834,8 +825,9 @@ std::vector<uint8_t> tree_rank_image(const taccl_plan &p) {
   for (int32_t o = 0; o < P; o++)
     for (int32_t v = 0; v < V; v++)
       for (int32_t d = 0; d < P; d++)
-        opt[4 * (o * a.opt_ostride + d / 4 * V + v) + d % 4] = p.topt[((size_t)o * V + v) * P + d];
-  if (C * V <= 512) std::copy(p.tent.begin(), p.tent.end(), b + a.o_ent);
+        opt[4 * (o * a.opt_ostride + d / 4 * V + v) + d % 4] = 
+            p.topt[((size_t)o * V + v) * p.topt_stride + d];
+  if (C * V <= 512) std::copy(p.tent.begin(), p.tent.begin() + P * V * P * K, b + a.o_ent);
   uint32_t *slot = (uint32_t *)(b + a.o_slot);
   for (int32_t c = 0; c < C; c++)
     for (int32_t v = 0; v < V; v++) {

@@ -673,6 +673,9 @@ struct TreeLds {
   const uint32_t *rt32;
   uint32_t *dist;
   uint16_t *anc;  // pj_rounds arrays of anc_stride slots: 2^k-th ancestor
+  // kEnt: entering link per (owner, vertex, destination, option), and the
+  // source of every link
+  const uint8_t *ent, *src;
 };
 
 // Trees, one lane per (chunk c, vertex v) slot (slots lane + 64j). The
@@ -687,12 +690,13 @@ struct TreeLds {
 // (Allgather) or, for ReduceScatter (kRS: costs of the reverse links), the
 // longest reversed path from below up to v. `bad`: a rank of the
 // postcondition is unreached; `fault` is never set (parents form a tree).
-template <int J, int PW, bool kRS>
+// kEnt: the entering link comes from a table instead of the 16-byte route
+// records, so routes may have any length and P need not be 4 * PW.
+template <int J, int PW, bool kRS, bool kEnt = false>
 __device__ __forceinline__ void slot_trees(const TreeArgs &a, const TreeLds &tl, int lane,
                                            uint32_t (&pe)[J], uint32_t (&ps)[J],
                                            uint32_t (&dv)[J], bool &bad, bool &fault) {
-  const int C = a.C, V = a.V, K = a.K;
-  constexpr int P = 4 * PW;
+  const int C = a.C, V = a.V, K = a.K, P = kEnt ? a.P : 4 * PW;
   const int CV = C * V;
   const uint32_t *s_cost = tl.cost;
   const uint8_t *s_own = tl.own;
@@ -718,7 +722,7 @@ __device__ __forceinline__ void slot_trees(const TreeArgs &a, const TreeLds &tl,
       const uint32_t sl = lane + 64 * (g0 + q);
       slc[q] = sl < (uint32_t)CV ? sl : 0u;
       c[q] = div_v(slc[q], a.vmagic);
-      v[q] = slc[q] - c[q] * V;
+      v[q] = slc[q] - __umul24(c[q], (uint32_t)V);
     }
 #pragma unroll
     for (int q = 0; q < G; q++) {
@@ -730,12 +734,16 @@ __device__ __forceinline__ void slot_trees(const TreeArgs &a, const TreeLds &tl,
     // lowest set bit is byte 4w + b of the smallest destination d whose
     // drawn path passes through v, and the bit inside the byte is that
     // path's option kd
-    uint32_t t[G][PW];
+    // (slots, vertices and table indexes stay far below 2^24: 24-bit multiplies
+    // issue at the full VALU rate)
+    uint32_t t[G][PW], ov[G];
+#pragma unroll
+    for (int q = 0; q < G; q++) ov[q] = __umul24(o[q], (uint32_t)V) + v[q];
 #pragma unroll
     for (int q = 0; q < G; q++)
 #pragma unroll
       for (int w = 0; w < PW; w++)
-        t[q][w] = rt32[c[q] * PW + w] & s_opt[(o[q] * V + v[q]) * PW + w];
+        t[q][w] = rt32[__umul24(c[q], (uint32_t)PW) + w] & s_opt[__umul24(ov[q], (uint32_t)PW) + w];
     uint32_t d[G], kd[G];
     bool has[G];
 #pragma unroll
@@ -755,12 +763,23 @@ __device__ __forceinline__ void slot_trees(const TreeArgs &a, const TreeLds &tl,
       d[q] = 4 * wi + (bit >> 3);
       kd[q] = bit & 7;
     }
+    uint32_t l[G], u[G];
+    if constexpr (kEnt) {
+#pragma unroll
+      for (int q = 0; q < G; q++)
+        l[q] = tl.ent[has[q] ? __umul24(__umul24(ov[q], (uint32_t)P) + d[q], (uint32_t)K) + kd[q]
+                             : 0u];
+#pragma unroll
+      for (int q = 0; q < G; q++) {
+        l[q] = has[q] ? l[q] : 0u;
+        u[q] = tl.src[l[q]];
+      }
+    }
     uint4 r[G];
 #pragma unroll
-    for (int q = 0; q < G; q++) r[q] = s_rec[(o[q] * P + d[q]) * K + kd[q]];
-    uint32_t l[G], u[G];
+    for (int q = 0; q < G && !kEnt; q++) r[q] = s_rec[(o[q] * P + d[q]) * K + kd[q]];
 #pragma unroll
-    for (int q = 0; q < G; q++) {
+    for (int q = 0; q < G && !kEnt; q++) {
       // the hop of that path that enters v
       const uint32_t x0 = r[q].x & 0xFFFFFFu, x1 = r[q].y, x2 = r[q].z, x3 = r[q].w;
       uint32_t e = x3, uu = (x2 >> 16) & 0xFFu;
@@ -782,15 +801,18 @@ __device__ __forceinline__ void slot_trees(const TreeArgs &a, const TreeLds &tl,
     // ReduceScatter measures the tree backwards, on reverse links
 #pragma unroll
     for (int q = 0; q < G; q++) ec[g0 + q] = s_cost[has[q] ? (kRS ? s_rev[l[q]] : l[q]) : 0u];
+    uint32_t cv[G];
+#pragma unroll
+    for (int q = 0; q < G; q++) cv[q] = __umul24(c[q], (uint32_t)V);
 #pragma unroll
     for (int q = 0; q < G; q++) {
       const int j = g0 + q;
       const bool top = u[q] == o[q];  // the parent is the chunk's owner
       pe[j] = has[q] ? (l[q] | (u[q] << 16)) : ~0u;
-      ps[j] = (has[q] && !top) ? c[q] * V + u[q] : kNoPred;
+      ps[j] = (has[q] && !top) ? cv[q] + u[q] : kNoPred;
       // ancestor chain: the parent's slot; the owner's slot (and a slot
       // without a send) is its own ancestor, with distance 0
-      an[j] = has[q] ? (top ? c[q] * V + o[q] : c[q] * V + u[q]) : slc[q];
+      an[j] = has[q] ? (top ? cv[q] + o[q] : cv[q] + u[q]) : slc[q];
       acc[j] = has[q] ? ec[j] : 0u;
       const uint32_t sl = lane + 64 * j;
       if (sl < (uint32_t)CV) {
@@ -995,7 +1017,8 @@ void tree_layers_kernel(TreeArgs a) {
     // pe: link | parent vertex << 16 of the send into the slot, ~0 if none
     uint32_t pe[J], ps[J], dv[J];
     bool bad = false, fault = false;
-    slot_trees<J, PW, kRS>(a, TreeLds{s_cost, s_own, s_post, s_rec, s_opt, s_rev, rt32, dist, anc},
+    slot_trees<J, PW, kRS>(a, TreeLds{s_cost, s_own, s_post, s_rec, s_opt, s_rev, rt32, dist, anc,
+                                      nullptr, nullptr},
                            lane, pe, ps, dv, bad, fault);
 
     // ---- keys and layers of this lane's sends ----------------------------
@@ -1554,7 +1577,7 @@ __global__ __launch_bounds__(kTreeMaxThreads) void tree_greedy_kernel(TreeArgs a
   uint8_t *s_src = lds + a.o_src;
   uint8_t *s_own = lds + a.o_own;
   uint64_t *s_post = (uint64_t *)(lds + a.o_post);
-  uint4 *s_rec = (uint4 *)(lds + a.o_rec4);
+  uint8_t *s_ent = lds + a.o_ent;  // entering link per (o, v, d, k)
   uint32_t *s_opt = (uint32_t *)(lds + a.o_opt);
   uint16_t *s_rev = (uint16_t *)(lds + a.o_rev);
   uint8_t *s_dst = lds + a.o_ldst;
@@ -1566,9 +1589,12 @@ __global__ __launch_bounds__(kTreeMaxThreads) void tree_greedy_kernel(TreeArgs a
       s_dst[j] = (uint8_t)a.ldst[j];
     }
   }
-  for (int r = threadIdx.x; r < 16 * PW * PW * a.K; r += blockDim.x) s_rec[r] = a.rec4[r];
-  for (int j = threadIdx.x; j < 4 * PW * V * PW; j += blockDim.x)
-    s_opt[j] = ((const uint32_t *)a.topt)[j];
+  // (both tables' bytes are padded to whole 16-byte groups in LDS and in
+  // global memory)
+  for (int r = threadIdx.x; r < (a.P * V * a.P * a.K + 15) / 16; r += blockDim.x)
+    ((uint4 *)s_ent)[r] = ((const uint4 *)a.ent)[r];
+  for (int j = threadIdx.x; j < (a.P * V * PW + 3) / 4; j += blockDim.x)
+    ((uint4 *)s_opt)[j] = ((const uint4 *)a.topt)[j];
   for (int j = threadIdx.x; j < C; j += blockDim.x) {
     s_own[j] = a.owner8[j];
     s_post[j] = a.post_mask[j];
@@ -1592,16 +1618,22 @@ __global__ __launch_bounds__(kTreeMaxThreads) void tree_greedy_kernel(TreeArgs a
 
   const int64_t stride = (int64_t)gridDim.x * a.waves_per_block;
   const int64_t first = (int64_t)blockIdx.x * a.waves_per_block + wave;
-  const int nrw = a.route_stride >> 2;
+  // A chunk's row of P route bytes takes PW words (loaded from any byte
+  // address; those that would pass the candidate's row are read from its
+  // last four bytes and shifted down when staged)
+  const int nrw = C * PW, pad = 4 * PW - a.P;
+  auto route_offset = [&](int j) -> int { return pad ? 4 * j - pad * (j / PW) : 4 * j; };
   uint32_t pf_r[kPfRoute], pf_p[J];
   auto prefetch = [&](int64_t i) {
     if (i >= a.n) return;
-    const uint32_t *g32 = (const uint32_t *)(a.routes + (size_t)i * a.route_stride);
+    const uint8_t *row = a.routes + (size_t)i * a.route_stride;
     const uint32_t *gpr = a.prio + (size_t)i * a.prio_stride;
 #pragma unroll
     for (int k = 0; k < kPfRoute; k++) {
       const int j = lane + 64 * k;
-      if (j < nrw) pf_r[k] = __builtin_nontemporal_load(g32 + j);
+      if (j < nrw)
+        pf_r[k] = __builtin_nontemporal_load(
+            (const u32_any *)(row + min(route_offset(j), a.route_stride - 4)));
     }
 #pragma unroll
     for (int k = 0; k < J; k++) {
@@ -1614,7 +1646,11 @@ __global__ __launch_bounds__(kTreeMaxThreads) void tree_greedy_kernel(TreeArgs a
 #pragma unroll
     for (int k = 0; k < kPfRoute; k++) {
       const int j = lane + 64 * k;
-      if (j < nrw) rt32[j] = one_hot_word<PW>(pf_r[k], j, s_post);
+      if (j < nrw) {
+        uint32_t w = pf_r[k];
+        if (pad) w >>= 8 * min(max(route_offset(j) - (a.route_stride - 4), 0), 3);
+        rt32[j] = one_hot_word<PW>(w, j, s_post);
+      }
     }
     uint32_t px[J];
 #pragma unroll
@@ -1625,8 +1661,9 @@ __global__ __launch_bounds__(kTreeMaxThreads) void tree_greedy_kernel(TreeArgs a
 
     uint32_t pe[J], ps[J], dv[J];
     bool bad = false, fault = false;
-    slot_trees<J, PW, kRS>(a, TreeLds{s_cost, s_own, s_post, s_rec, s_opt, s_rev, rt32, dist, anc},
-                           lane, pe, ps, dv, bad, fault);
+    slot_trees<J, PW, kRS, true>(a, TreeLds{s_cost, s_own, s_post, nullptr, s_opt, s_rev, rt32, dist,
+                                            anc, s_ent, s_src},
+                                 lane, pe, ps, dv, bad, fault);
 
     // ---- per-slot send records; sends counted per link ------------------
     const bool mirror = a.greedy == 2;
@@ -1952,13 +1989,37 @@ hipError_t launch_tree_layers(const TreeArgs &a, int grid, hipStream_t stream) {
 }
 
 int32_t tree_greedy_layout(const taccl_plan &p, TreeArgs &a) {
-  if (tree_layers_layout(p, a) <= 0) return 0;
-  const int32_t C = p.coll.C, V = p.topo.V, E = p.topo.E;
-  const int32_t CV = C * V;
-  if (E > 64 * kGreedyLinkSlots) return 0;
-  uint32_t cmin = ~0u;
-  for (uint32_t c : p.cost) cmin = std::min(cmin, c);
+  if (tree_layout(p, a) <= 0) return 0;
+  const int32_t C = p.coll.C, V = p.topo.V, E = p.topo.E, P = p.topo.P;
+  const int32_t CV = C * V, K = std::max(p.max_paths, 1), pw = rank_words(P);
+  // Any rank count up to 32 and any route length. Where both fit, the general
+  // kernel, whose trees are built chunk by chunk along the routes, takes 121
+  // us against 88 (8000 Allgathers on two 7-rank nodes), 424 against 278 (two
+  // 9-rank switches, reverse path order) and the same 155 us on a 12-rank
+  // ring, whose time is all windows.
+  if (p.topt.empty() || p.tent.empty() || K > 8 || P > 32 || V > 64 || E < 1 ||
+      E > 64 * kGreedyLinkSlots || CV > 64 * kLayerMaxSlotsPerLane || C * pw > 64 * kPfRoute ||
+      p.route_stride < 4)
+    return 0;
+  uint32_t cmin = ~0u, cmax = 0;
+  for (uint32_t c : p.cost) {
+    cmin = std::min(cmin, c);
+    cmax = std::max(cmax, c);
+  }
+  if (cmin == 0 || (uint64_t)(V - 1) * cmax >= (1ull << 32)) return 0;
   a.cmin = cmin;
+  // shared tables: entering links and option bytes in place of the
+  // fixed-stride records
+  int32_t off = a.o_rec;
+  a.o_ent = off;
+  off = align16(off + P * V * P * K);
+  a.o_opt = off;
+  off = align16(off + 4 * P * V * pw);
+  a.o_rev = off;
+  off = align16(off + 2 * E);
+  a.o_ldst = off;
+  off = align16(off + E);
+  a.o_wave = off;
   const int32_t S = std::max<int64_t>(std::min<int64_t>(p.max_sends, CV), 1);
   int32_t w = 0;
   auto wtake = [&](int32_t bytes) {
@@ -1980,7 +2041,7 @@ int32_t tree_greedy_layout(const taccl_plan &p, TreeArgs &a) {
   set_pj(a, V, CV);
   const int32_t u = w;
   a.w_rt = u;
-  a.w_dist = u + align16(p.route_stride);
+  a.w_dist = u + align16(4 * C * pw);
   a.w_anc = a.w_dist + align16(4 * CV);
   a.w_glist = u;
   a.wave_bytes = std::max(a.w_anc + a.pj_rounds * align16(2 * CV), u + align16(16 * S));
@@ -2001,7 +2062,7 @@ static const void *greedy_fn_j(int pw) {
 
 template <bool kR>
 static const void *greedy_fn_r(const TreeArgs &a) {
-  const int J = (a.C * a.V + 63) / 64, pw = a.P / 4;
+  const int J = (a.C * a.V + 63) / 64, pw = rank_words(a.P);
   if (J <= 1) return greedy_fn_j<1, kR>(pw);
   if (J <= 2) return greedy_fn_j<2, kR>(pw);
   if (J <= 4) return greedy_fn_j<4, kR>(pw);
@@ -2062,8 +2123,7 @@ int tree_greedy_blocks_per_cu(const TreeArgs &a) {
 }
 
 hipError_t launch_tree_greedy(const TreeArgs &a, int grid, hipStream_t stream) {
-  const int pw = a.P / 4;
-  if (a.P % 4 || (pw != 1 && pw != 2 && pw != 3 && pw != 4 && pw != 6 && pw != 8)) return hipErrorInvalidValue;
+  if (a.P > 32 || a.C * a.V > 64 * kLayerMaxSlotsPerLane) return hipErrorInvalidValue;
   const dim3 g(grid), b(64 * a.waves_per_block);
   void *args[] = {(void *)&a};
   return hipLaunchKernel(greedy_fn(a), g, b, args, tree_block_bytes(a, a.waves_per_block),

@@ -191,6 +191,16 @@ struct ConnArgs {
   int32_t cells, nwords, lanes, nrec, rec_lds, routes_words;
 };
 
+// Four route bytes from any byte address in one load
+typedef uint32_t __attribute__((aligned(1))) u32_any;
+
+// Route words per chunk of the slot-parallel multicast instantiations (1, 2,
+// 3, 4, 6 or 8) that run P <= 32 ranks
+inline int rank_words(int P) {
+  const int w = (P + 3) / 4;
+  return w == 5 ? 6 : w == 7 ? 8 : w;
+}
+
 constexpr int kConnMaxThreads = 256;
 constexpr int kConnWaveThreads = 1024;
 // record tables up to this size are copied to LDS by every block

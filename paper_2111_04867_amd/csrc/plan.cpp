@@ -868,8 +868,9 @@ static taccl_status_t build_layout(taccl_plan *p) {
         for (int32_t j = 0; j < H; j++) p->tree_rec4[r * 4 + j] = p->tree_rec[r * H + j];
     }
     p->tent.clear();
-    if (t.E <= 255) {
-      p->tent.assign((size_t)P * V * P * K, 0xFF);
+    if (t.E <= 256) {
+      p->tent.assign(((size_t)P * V * P * K + 15) / 16 * 16, 0xFF);
+      std::vector<uint8_t> entered(p->tent.size(), 0);
       for (int32_t o = 0; o < P; o++)
         for (int32_t d = 0; d < P; d++) {
           const int32_t pp = o * P + d;
@@ -879,8 +880,9 @@ static taccl_status_t build_layout(taccl_plan *p) {
             // legs); the first-reach merge takes the first entry
             for (uint32_t j = p->path_off[q]; j < p->path_off[q + 1]; j++) {
               const uint16_t l = p->path_links[j];
-              uint8_t &slot = p->tent[(((size_t)o * V + p->ldst[l]) * P + d) * K + k];
-              if (slot == 0xFF) slot = (uint8_t)l;
+              const size_t slot = (((size_t)o * V + p->ldst[l]) * P + d) * K + k;
+              if (!entered[slot]) p->tent[slot] = (uint8_t)l;
+              entered[slot] = 1;
             }
           }
         }
@@ -888,7 +890,9 @@ static taccl_status_t build_layout(taccl_plan *p) {
     path_sum_codes(p);
     p->topt.clear();
     if (K <= 8) {
-      p->topt.assign((size_t)P * V * P, 0);
+      p->topt_stride = P <= 32 ? 4 * rank_words(P) : P;
+      // (whole 16-byte groups, as the kernels copy it)
+      p->topt.assign(((size_t)P * V * p->topt_stride + 15) / 16 * 16, 0);
       for (int32_t o = 0; o < P; o++)
         for (int32_t d = 0; d < P; d++) {
           const int32_t pp = o * P + d;
@@ -896,7 +900,7 @@ static taccl_status_t build_layout(taccl_plan *p) {
             const uint32_t q = p->pair_base[pp] + k;
             for (uint32_t j = p->path_off[q]; j < p->path_off[q + 1]; j++) {
               const int32_t v = p->ldst[p->path_links[j]];
-              p->topt[((size_t)o * V + v) * P + d] |= (uint8_t)(1u << k);
+              p->topt[((size_t)o * V + v) * p->topt_stride + d] |= (uint8_t)(1u << k);
             }
           }
         }

@@ -135,9 +135,10 @@ struct taccl_plan {
   // the first word); options a pair does not have are all zero (no hops)
   std::vector<uint32_t> tree_rec;
   std::vector<uint8_t> owner8;      // [C] owner rank of every chunk
-  // [(o*V + v)*P + d]: bit k set when option k of pair (o, d) passes
+  // [(o*V + v)*topt_stride + d] (a row is whole route words): bit k set when option k of pair (o, d) passes
   // through vertex v (v != o); empty unless every pair has at most 8 options
   std::vector<uint8_t> topt;
+  int32_t topt_stride = 0;
   // the route records again with 4 words per option (zero padded), for
   // plans with at most 4 hops
   std::vector<uint32_t> tree_rec4;

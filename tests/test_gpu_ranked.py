@@ -126,3 +126,33 @@ def test_three_mesh_nodes():
     for x in kinds(w):
         check(x, n=150)
     check(cf.with_contiguity(w), n=150)
+
+
+# the same plans under time-aware greedy orders, in path and reverse path order
+@pytest.mark.parametrize("order", [cf.with_greedy, cf.with_reverse_greedy],
+                         ids=["greedy", "reverse"])
+@pytest.mark.parametrize("P", [3, 5, 6, 9, 14, 17, 22])
+def test_greedy_rank_counts_and_long_routes(P, order):
+    for w in kinds(ring(P)):
+        check(order(w), n=33)
+    check(order(cf.full_ag(min(P, 14), k=3)), n=33, shift=P % 4)
+
+
+@pytest.mark.parametrize("order", [cf.with_greedy, cf.with_reverse_greedy],
+                         ids=["greedy", "reverse"])
+@pytest.mark.parametrize("P,C", [(8, 8), (13, 5), (9, 14), (16, 16), (10, 26), (7, 73), (16, 32),
+                                 (27, 19), (15, 35)])
+def test_greedy_slot_counts(P, C, order):
+    """Slots per lane 1, 2, 4 and 8, up to 512 slots, and the first plans past
+    them."""
+    check(order(broadcast(cf.full_ag(P, k=2) if P != 27 else ring(P), C)), n=33)
+
+
+@pytest.mark.parametrize("order", [cf.with_greedy, cf.with_reverse_greedy],
+                         ids=["greedy", "reverse"])
+@pytest.mark.parametrize("per,cpr,kib", [(3, 1, 17), (5, 1, 333), (6, 2, 4)])
+def test_greedy_two_nodes(per, cpr, kib, order):
+    base = cf.two_node_full(per, cf.ALLGATHER, cpr, k=3, chunk_bytes=1024 * kib, contiguity=0)
+    w = replace(base, max_cross=1, relay=np.ones(2 * per, dtype=np.uint8))
+    for x in kinds(w):
+        check(order(x), n=33)
