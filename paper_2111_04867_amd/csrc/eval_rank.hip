@@ -18,10 +18,13 @@
 //      (the travelled length of Sec. 5.1) and every tree height (the
 //      remaining length is the link's cost plus the height below v);
 //   3. keys: both lengths are sums of at most V - 1 link costs, and a plan
-//      constant maps every such sum to an exact 11-bit code that preserves
-//      order, so one 64-bit word (remaining code descending, travelled code
+//      constant maps every such sum to an exact code that preserves order,
+//      so one 64-bit word (remaining code descending, travelled code
 //      ascending, priority, slot) orders a link's sends exactly as the
-//      Step-2 rule (remaining desc, travelled asc, priority, chunk);
+//      Step-2 rule (remaining desc, travelled asc, priority, chunk). Only
+//      sends of one layer (below) are ever compared, so the remaining
+//      length counts from the layer's far end: a code of fewer bits, which
+//      leaves more of the 22 that both have to the travelled length;
 //   4. layers: layer = floor(rem / c_min); a parent send's remaining length
 //      exceeds its child's by at least one link cost, so parents lie in
 //      higher layers and every dependency inside a layer runs along a link.
@@ -361,7 +364,8 @@ __global__ __launch_bounds__(rank_max_threads<J>()) void tree_rank_kernel(TreeAr
         hh[j] = hgt[lane + 64 * j];
         cl[j] = s_cost[pl[j] != ~0u ? pl[j] & 0xFFu : 0u];
       }
-      const uint32_t top = (uint32_t)a.qrange - 1;
+      const uint32_t top = (uint32_t)a.qrange - 1, cmin = a.cmin;
+      const int rem_shift = a.rem_shift;
       const uint32_t lmag = (uint32_t)a.lmagic, qmag = (uint32_t)a.qmagic;
 #pragma unroll
       for (int j = 0; j < J; j++) {
@@ -371,16 +375,19 @@ __global__ __launch_bounds__(rank_max_threads<J>()) void tree_rank_kernel(TreeAr
           const uint32_t trav = kR ? hh[j] : acc[j] - cl[j];
           const uint32_t rem = kR ? acc[j] : cl[j] + hh[j];
           uint32_t L = __umulhi(rem, lmag);
-          const uint32_t rq = __umulhi(rem, qmag);
+          // distance to the layer's far end (L is floor(rem / c_min) or, by
+          // the rounded-up multiplier, one more)
+          const uint32_t far = __umul24(L, cmin) + (cmin - 1) - rem;
+          const uint32_t rq = __umulhi(far, qmag);
           const uint32_t tq = __umulhi(trav, qmag);
-          if (L >= (uint32_t)a.nl_max || rq > top || tq > top) {  // unreachable (plan bounds)
+          if (L >= (uint32_t)a.nl_max || tq > top) {  // unreachable (plan bounds)
             L = 0;
             fault = 1;
           }
           const uint32_t u = (pl[j] >> 8) & 63u, own = (pl[j] >> 14) & 63u;
           const uint32_t pjs_v = u == own ? kNone : (pl[j] >> 20) - own + u;
           bl[j] = (pl[j] & 0xFFu) | (L << 8) | (pjs_v << 16);
-          const uint32_t hi = ((top - rq) << 21) | (tq << 10) | (px[j] >> 22);
+          const uint32_t hi = (rq << rem_shift) | (tq << 10) | (px[j] >> 22);
           const uint32_t lo = (px[j] << 10) | (uint32_t)(lane + 64 * j);
           key[j] = ((uint64_t)hi << 32) | lo;
           lm |= 1ull << L;
@@ -490,9 +497,11 @@ __global__ __launch_bounds__(rank_max_threads<J>()) void tree_rank_kernel(TreeAr
           const uint32_t before = (uint32_t)((y + t < be) & (m[t] < kx));
           rank += before;
           // an earlier send of the bucket with the same remaining length
-          // (the code in the key's top 11 bits; equal lengths sort next to
-          // each other)
-          if (kC) same |= before & (uint32_t)((m[t] >> 53) == (kx >> 53));
+          // (the code at the key's top; equal lengths sort next to each
+          // other)
+          if (kC)
+            same |= before & (uint32_t)(((uint32_t)(m[t] >> 32) >> a.rem_shift) ==
+                                        ((uint32_t)(kx >> 32) >> a.rem_shift));
         }
       }
       const uint32_t q = bs + rank;
@@ -742,6 +751,22 @@ int32_t tree_rank_layout(const taccl_plan &p, TreeArgs &a) {
   a.nl_max = (int32_t)nl;
   a.qmagic = p.pq_magic;
   a.qrange = p.pq_range;
+  a.cmin = (uint32_t)cmin;
+  // The key's 22 bits for both codes: as many as the travelled lengths' take,
+  // the rest for the distance of a remaining length x to its layer's far end,
+  // (L + 1) c_min - 1 - x. L <= x (2^32 + e) / (2^32 c_min) with e = lmagic *
+  // c_min - 2^32, so L c_min passes x by at most x e / 2^32. With 11 bits for
+  // each code over the whole path, plans whose costs lie close to a common
+  // multiple (a crossing of 12.99 links inside a node) had no codes and ran
+  // on the layered or the general kernel: 52758 contiguous Allgathers on
+  // three such 10-rank switches 6313 -> 2007 us, other plans the same.
+  int tbits = 0, rbits = 0;
+  while ((1ll << tbits) < p.pq_range) tbits++;
+  const uint64_t past = (max_rem * (a.lmagic * cmin - (1ull << 32))) >> 32;
+  const uint64_t far_codes = (((cmin - 1 + past) * p.pq_magic) >> 32) + 1;
+  while ((1ull << rbits) < far_codes) rbits++;
+  if (tbits + rbits > 22) return 0;
+  a.rem_shift = 10 + tbits;
   a.K = K;
   a.H = H;
   int32_t off = 0;

@@ -61,10 +61,11 @@ struct TreeArgs {
   // order, and the per-link state of open contiguous transfers
   int32_t any, greedy, w_gst;
   // ranked variant: exact order-preserving codes of path lengths
-  // (code = (x * qmagic) >> 32 < qrange), the entering-link table, the
+  // (code = (x * qmagic) >> 32 < qrange) and the place of the remaining
+  // length's code in a key's upper word, the entering-link table, the
   // per-slot heights and the parent send of each bucket-sorted position
   uint64_t qmagic;
-  int32_t qrange;
+  int32_t qrange, rem_shift;
   const uint4 *rank_img;  // the block's shared LDS below o_wave, ready to copy
   const uint8_t *ent;
   int32_t o_rcost, o_ent, w_h, o_slot, opt_ostride, w_pj;
@@ -213,6 +214,7 @@ constexpr int kTreeMaxThreads = 512;  // up to 8 wavefronts per block
 constexpr int kLayerMaxSlotsPerLane = 8;
 constexpr int kRankMaxThreads = 768;  // ranked multicast kernel: up to 12
 constexpr int kRankMaxSlots = 1024;   // its (chunk, vertex) slots: 16 per lane
+constexpr int kRankMaxRange = 1 << 21;  // its codes of a path length (22 key bits hold two)
 constexpr int kTreeRecLdsMax = 32768;  // route records kept in LDS up to this size
 constexpr int kPathThreads = 256;
 constexpr int kPathPortThreads = 1024;  // LDS-record kernel on switch-port plans

@@ -711,7 +711,7 @@ static int32_t tree_crossings(const taccl_plan *p) {
 // of S and m = ceil(2^32 / g), x -> floor(x * m / 2^32) is nondecreasing
 // everywhere and gains at least 1 per step of S (g * m >= 2^32), so it
 // orders and separates S exactly. Left at range 0 when S exceeds 16384
-// elements or the codes need more than 11 bits.
+// elements or the codes alone overfill the ranked kernel's keys.
 static void path_sum_codes(taccl_plan *p) {
   p->pq_magic = 0;
   p->pq_range = 0;
@@ -754,7 +754,7 @@ static void path_sum_codes(taccl_plan *p) {
   for (size_t i = 1; i < S.size(); i++)
     if (code(S[i]) <= code(S[i - 1])) return;  // cannot happen (see above)
   const uint64_t range = code(S.back()) + 1;
-  if (range > 2048) return;
+  if (range > kRankMaxRange) return;
   p->pq_magic = m;
   p->pq_range = (int32_t)range;
   p->pq_max = S.back();

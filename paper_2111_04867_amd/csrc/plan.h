@@ -152,7 +152,7 @@ struct taccl_plan {
   // remaining or travelled length of a multicast send is a sum of at most
   // V - 1 link costs, and x -> (x * pq_magic) >> 32 is strictly increasing
   // on the set of such sums, with values below pq_range (0: the set is too
-  // large or too dense for 11-bit codes)
+  // large or too dense for codes of a key)
   uint64_t pq_magic = 0;
   int32_t pq_range = 0;
   uint64_t pq_max = 0;  // the largest such sum

@@ -128,6 +128,28 @@ def test_three_mesh_nodes():
     check(cf.with_contiguity(w), n=150)
 
 
+# Crossings that cost just under 13 links inside a node: the gap `short`
+# between sums sets the codes' bits. 29000 per link and 13 x 29000 - short per
+# crossing take 10 + 6 bits, 11 + 7, 13 + 8 and 13 + 9 (the most a key holds),
+# then more than it holds (the layered or general kernel, as before)
+@pytest.mark.parametrize("short", [900, 345, 120, 88, 80, 7, 1])
+@pytest.mark.parametrize("per,cpr", [(6, 1), (8, 1), (6, 2)])
+def test_code_bits(short, per, cpr):
+    P = 2 * per
+    edges = [(n * per + i, n * per + j, 29000, 0) for n in (0, 1) for i in range(per)
+             for j in range(per) if i != j]
+    edges += [(s, (s + per) % P, 13 * 29000 - short - 109, 106) for s in (0, 1, per, per + 1)]
+    row_ptr, col, a, b = cf.csr_from_edges(P, edges)
+    relay = np.zeros(P, dtype=np.uint8)
+    relay[[0, 1, per, per + 1]] = 1
+    w = cf.Workload(f"codes{short}", P, P, row_ptr, col, a, b,
+                    np.array([r // per for r in range(P)], dtype=np.int32), cf.ALLGATHER, cpr,
+                    1024, cf.KSHORTEST, k=3, max_cross=1, relay=relay)
+    for x in kinds(w):
+        check(x, n=70)
+    check(cf.with_contiguity(w), n=70)
+
+
 # the same plans under time-aware greedy orders, in path and reverse path order
 @pytest.mark.parametrize("order", [cf.with_greedy, cf.with_reverse_greedy],
                          ids=["greedy", "reverse"])
