@@ -34,11 +34,11 @@ TARGETS = ("twonode16_ag", "fournode64_a2a")
 # Kernel that dominates each workload's launch (the only kernel it runs).
 KERNEL_OF = {"ring4_ag": "tree_rank", "cubemesh8_ag": "tree_rank",
              "twonode16_ag": "tree_rank", "switch16_a2a": "path_eval_fast",
-             "fournode64_a2a": "path_eval_fast", "twonode16_ag_contig": "tree_layers",
-             "fournode64_a2a_contig": "path_eval_fast", "cubemesh8_ar": "tree_layers",
-             "twonode16_rs": "tree_layers", "twonode16_ar": "tree_layers",
+             "fournode64_a2a": "path_eval_fast", "twonode16_ag_contig": "tree_rank",
+             "fournode64_a2a_contig": "path_eval_fast", "cubemesh8_ar": "tree_rank",
+             "twonode16_rs": "tree_rank", "twonode16_ar": "tree_rank",
              "cubemesh8_ag_greedy": "tree_greedy", "twonode16_ag_greedy": "tree_greedy",
-             "switch16_a2a_ports": "path_eval", "fournode64_a2a_ports": "path_eval",
+             "switch16_a2a_ports": "path_eval_ports", "fournode64_a2a_ports": "path_eval_ports",
              "switch16_a2a_greedy": "path_greedy", "fournode64_a2a_greedy": "path_greedy_block",
              "twonode16_ag_rgreedy": "tree_greedy"}
 
