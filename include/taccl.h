@@ -222,6 +222,14 @@ typedef struct {
  */
 taccl_status_t taccl_plan_info(taccl_plan_t plan, taccl_plan_info_t *out);
 
+/* The kernels that evaluate the plan's candidates ("tree_eval",
+ * "tree_layers", "tree_greedy", "tree_rank", "path_eval", "path_eval_fast",
+ * "path_eval_ports", "path_greedy", "path_greedy_block"; "none" where
+ * evaluation refuses the plan), joined by '+' for the two phases of an
+ * Allreduce, for routes that start on a word. Owned by the plan; "" for
+ * null. */
+const char *taccl_plan_kernels(taccl_plan_t plan);
+
 /* options[route_stride]: number of route options of every route entry
  * (0 for entries no pair uses). */
 taccl_status_t taccl_plan_route_options(taccl_plan_t plan, int32_t *options);

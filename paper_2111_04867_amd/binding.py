@@ -46,7 +46,8 @@ class PlanInfo(ct.Structure):
 # every symbol include/taccl.h declares
 EXPORTS = ["taccl_topology_create", "taccl_topology_destroy", "taccl_collective_create",
            "taccl_collective_create_explicit", "taccl_collective_destroy", "taccl_sketch_apply",
-           "taccl_plan_destroy", "taccl_plan_info", "taccl_plan_route_options",
+           "taccl_plan_destroy", "taccl_plan_info", "taccl_plan_kernels",
+           "taccl_plan_route_options",
            "taccl_plan_path", "taccl_plan_link_costs", "taccl_plan_upload", "taccl_eval_batch",
            "taccl_connections_batch", "taccl_generate_host", "taccl_count_faults",
            "taccl_last_error",
@@ -84,6 +85,8 @@ def lib():
     L.taccl_plan_destroy.argtypes = [P]
     L.taccl_plan_info.restype = st
     L.taccl_plan_info.argtypes = [P, ct.POINTER(PlanInfo)]
+    L.taccl_plan_kernels.restype = ct.c_char_p
+    L.taccl_plan_kernels.argtypes = [P]
     L.taccl_plan_route_options.restype = st
     L.taccl_plan_route_options.argtypes = [P, P]
     L.taccl_plan_path.restype = st
@@ -198,6 +201,11 @@ class Plan:
             self._h = None
 
     # ---- host views ------------------------------------------------------
+    @property
+    def kernels(self):
+        """Names of the kernels that evaluate the plan (taccl_plan_kernels)."""
+        return lib().taccl_plan_kernels(self._h).decode()
+
     def route_options(self):
         out = np.zeros(self.route_stride, dtype=np.int32)
         _check(lib().taccl_plan_route_options(self._h, _np_ptr(out)))

@@ -118,10 +118,10 @@ taccl_status_t ensure_device(taccl_plan *p, DeviceTables **out) {
 // by LDS, the 32 wavefronts of a CU and the runtime's occupancy query
 // (per_cu(waves); 0 if it fails). bytes(waves): LDS of a block.
 template <class Bytes, class PerCu>
-LaunchShape launch_shape(taccl_plan *p, DeviceTables *t, ShapeOf which, int max_waves, Bytes bytes,
-                         PerCu per_cu) {
+LaunchShape launch_shape(taccl_plan *p, DeviceTables *t, Kernel kernel, bool reduce, int max_waves,
+                         Bytes bytes, PerCu per_cu) {
   std::lock_guard<std::mutex> lock(p->mu);
-  LaunchShape &s = t->shape[which];
+  LaunchShape &s = t->shape[kernel][reduce];
   if (s.waves) return s;
   LaunchShape best{1, 1};
   int best_res = 0;
@@ -182,12 +182,14 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
   const int64_t cap = (int64_t)std::max(t->num_cus, 1) * 64;
   const int grid = (int)std::min<int64_t>(n, cap);
   hipError_t e;
+  const bool route_words = (p->route_stride % 4 == 0) && (((uintptr_t)d_routes & 3) == 0);
+  PathArgs a{};
+  PathGreedyArgs g{};
+  PortsArgs pa{};
+  const Kernel kernel =
+      p->coll.kind == TACCL_ALLTOALL ? path_select(*p, t->max_lds, a, g, pa) : kNoKernel;
   if (p->coll.kind == TACCL_ALLTOALL && p->greedy) {
-    PathGreedyArgs g{};
-    // one wavefront per candidate while its lists fit, else one block
-    const bool wave =
-        path_greedy_layout(*p, g) > 0 && g.o_wave + g.wave_bytes <= t->max_lds;
-    if (!wave && (path_greedy_block_layout(*p, g) <= 0 || g.block_bytes > t->max_lds))
+    if (kernel == kNoKernel)
       return fail(TACCL_ERR_UNSUPPORTED,
                   "time-aware greedy orders for Alltoall need at most 65535 send slots "
                   "(chunks x longest path), 4096 chunks and no zero-cost link");
@@ -210,10 +212,10 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     g.makespan = d_makespan;
     g.valid = d_valid;
     g.n = n;
-    if (!wave) {
+    if (kernel == kPathGreedyBlock) {
       // the block kernel has one size: only its resident blocks are asked for
       const LaunchShape sh = launch_shape(
-          p, t, kShapePathGreedyBlock, 1, [&](int) { return g.block_bytes; },
+          p, t, kernel, false, 1, [&](int) { return g.block_bytes; },
           [&](int) { return path_greedy_block_per_cu(g); });
       const int bgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
       e = launch_path_greedy_block(g, bgrid, s);
@@ -222,7 +224,7 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     }
     // wavefronts per block: most resident wavefronts per CU
     const LaunchShape sh = launch_shape(
-        p, t, kShapePathGreedy, kTreeMaxThreads / 64,
+        p, t, kernel, false, kTreeMaxThreads / 64,
         [&](int w) { return g.o_wave + w * g.wave_bytes; },
         [&](int w) {
           g.waves_per_block = w;
@@ -235,15 +237,13 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return TACCL_OK;
   }
-  PortsArgs pa{};
-  if (p->ports && path_ports_layout(*p, pa) > 0 && pa.lds_bytes <= t->max_lds &&
-      path_ports_supported(*p, t->max_lds)) {
+  if (kernel == kPathPorts) {
     pa.C = p->coll.C;
     pa.H = std::max(p->H, 1);
     pa.nlev = p->nlev;
     pa.route_stride = p->route_stride;
     pa.prio_stride = p->prio_stride;
-    pa.routes_words = (p->route_stride % 4 == 0) && (((uintptr_t)d_routes & 3) == 0);
+    pa.routes_words = route_words;
     pa.cost = t->cost;
     pa.arec = t->arec;
     pa.cpath = t->cpath;
@@ -258,12 +258,15 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     pa.valid = d_valid;
     pa.n = n;
     const LaunchShape sh = launch_shape(
-        p, t, kShapePathPorts, 1, [&](int) { return pa.lds_bytes; },
+        p, t, kernel, false, 1, [&](int) { return pa.lds_bytes; },
         [&](int) { return path_ports_blocks_per_cu(pa); });
     const int pgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
     e = launch_path_ports(pa, pgrid, s);
   } else if (p->coll.kind == TACCL_ALLTOALL) {
-    PathArgs a{};
+    if (kernel == kNoKernel)
+      return fail(TACCL_ERR_UNSUPPORTED,
+                  a.lds_bytes > t->max_lds ? "Alltoall plan needs more LDS than a block has"
+                                           : "switch ports take at most four links per thread");
     a.C = p->coll.C;
     a.P = p->topo.P;
     a.E = p->topo.E;
@@ -299,137 +302,92 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     a.cls2_link = t->cls2_link;
     a.arec = t->arec;
     a.cpath = t->cpath;
-    a.routes_words = (p->route_stride % 4 == 0) && (((uintptr_t)d_routes & 3) == 0);
+    a.routes_words = route_words;
     a.cinfo = t->cinfo;
     a.cbkt = t->cbkt;
-    const int cpt = p->path_fast ? path_fast_cpt(*p) : 0;
-    if (cpt && path_fast_layout(*p, a) <= t->max_lds) {
-      const int nt = path_fast_threads(*p);
+    if (kernel == kPathFast) {
+      const int cpt = path_fast_cpt(*p), nt = path_fast_threads(*p);
       const LaunchShape sh = launch_shape(
-          p, t, kShapePathFast, 1, [&](int) { return a.lds_bytes; },
+          p, t, kernel, false, 1, [&](int) { return a.lds_bytes; },
           [&](int) { return path_fast_blocks_per_cu(a, cpt, nt); });
       const int fgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
       e = launch_path_fast(a, cpt, nt, fgrid, s);
     } else {
-      if (path_layout(*p, a) > t->max_lds)
-        return fail(TACCL_ERR_UNSUPPORTED, "Alltoall plan needs more LDS than a block has");
-      if (a.ports && !path_ports_supported(*p, t->max_lds))
-        return fail(TACCL_ERR_UNSUPPORTED, "switch ports take at most four links per thread");
       e = launch_path(a, grid, s);
     }
   } else {
-    TreeArgs a{};
-    a.C = p->coll.C;
-    a.P = p->topo.P;
-    a.V = p->topo.V;
-    a.E = p->topo.E;
-    a.route_stride = p->route_stride;
-    a.prio_stride = p->prio_stride;
-    a.routes_word_aligned = (p->route_stride % 4 == 0) && (((uintptr_t)d_routes & 3) == 0);
-    a.cost = t->cost;
-    a.lsrc = t->lsrc;
-    a.ldst = t->ldst;
-    a.rec = t->tree_rec;
-    a.npaths = t->npaths;
-    a.owner8 = t->owner8;
-    a.topt = t->topt;
-    a.contig = p->contig;
-    a.lalpha = t->lalpha;
-    a.lbs = t->lbs;
-    a.lmerge = t->lmerge;
-    a.rec4 = (const uint4 *)t->tree_rec4;
-    a.post_mask = t->post_mask;
-    a.routes = d_routes;
-    a.prio = d_prio;
-    a.makespan = d_makespan;
-    a.valid = d_valid;
-    a.n = n;
-    a.ent = t->tent;
-    // the layered kernel needs whole route words and priorities in registers
-    const bool greedy = p->greedy != 0;
-    const bool layered = (greedy ? tree_greedy_layout(*p, a) > 0
-                                 : a.routes_word_aligned && tree_layers_layout(*p, a) > 0) &&
-                         tree_block_bytes(a, 1) <= t->max_lds;
+    TreeArgs x{};
+    x.C = p->coll.C;
+    x.P = p->topo.P;
+    x.V = p->topo.V;
+    x.E = p->topo.E;
+    x.route_stride = p->route_stride;
+    x.prio_stride = p->prio_stride;
+    x.routes_word_aligned = route_words;
+    x.cost = t->cost;
+    x.lsrc = t->lsrc;
+    x.ldst = t->ldst;
+    x.lrev = t->lrev;
+    x.rec = t->tree_rec;
+    x.npaths = t->npaths;
+    x.owner8 = t->owner8;
+    x.topt = t->topt;
+    x.ent = t->tent;
+    x.rank_img = (const uint4 *)t->rank_img;
+    x.contig = p->contig;
+    x.greedy = p->greedy;
+    x.lalpha = t->lalpha;
+    x.lbs = t->lbs;
+    x.lmerge = t->lmerge;
+    x.rec4 = (const uint4 *)t->tree_rec4;
+    x.post_mask = t->post_mask;
+    x.routes = d_routes;
+    x.makespan = d_makespan;
+    x.valid = d_valid;
+    x.n = n;
+    // An Allreduce is a ReduceScatter on the first priority row, then an
+    // Allgather on the second, adding its makespan (same stream, so in order);
+    // both kernels are chosen before the first is launched
+    TreeArgs phase[2];
+    Kernel kernels[2];
+    int phases = 0;
     const int kind = p->coll.kind;
-    const bool reduction = kind == TACCL_REDUCESCATTER || kind == TACCL_ALLREDUCE;
-    // plans outside the layered kernel's limits: the general kernel, whose
-    // variant with reductions, contiguity and greedy orders keeps more state
-    a.any = !layered && (reduction || p->contig || greedy);
-    a.greedy = p->greedy;
-    if (!layered && (a.any ? tree_any_layout(*p, a) : tree_layout(*p, a)) > t->max_lds)
-      return fail(TACCL_ERR_UNSUPPORTED, "multicast plan needs more LDS than a block has");
-    a.lrev = t->lrev;
-    // wavefronts per block: most resident wavefronts per CU (LDS, and for
-    // the layered kernel registers too, by the runtime's occupancy query)
-    auto launch = [&](TreeArgs &x) {
-      const ShapeOf which = layered ? (x.reduce ? kShapeLayersReduce : kShapeLayers)
-                                    : (x.reduce ? kShapeTreeReduce : kShapeTree);
+    for (int reduce = 1; reduce >= 0; reduce--) {
+      if (reduce ? kind != TACCL_REDUCESCATTER && kind != TACCL_ALLREDUCE
+                 : kind == TACCL_REDUCESCATTER)
+        continue;
+      TreeArgs &y = phase[phases] = x;
+      y.reduce = reduce;
+      y.accumulate = phases;
+      y.prio = d_prio + (size_t)phases * p->coll.C * p->topo.V;
+      kernels[phases] = tree_select(*p, reduce, route_words, t->max_lds, y);
+      if (kernels[phases++] == kNoKernel)
+        return fail(TACCL_ERR_UNSUPPORTED, "multicast plan needs more LDS than a block has");
+    }
+    e = hipSuccess;
+    for (int i = 0; i < phases && e == hipSuccess; i++) {
+      TreeArgs &y = phase[i];
+      const Kernel k = kernels[i];
+      // wavefronts per block: most resident wavefronts per CU (LDS, and but
+      // for the general kernel registers too, by the runtime's occupancy query)
       const LaunchShape sh = launch_shape(
-          p, t, which, kTreeMaxThreads / 64, [&](int w) { return tree_block_bytes(x, w); },
+          p, t, k, y.reduce != 0, k == kTreeRank ? tree_rank_max_waves(y) : kTreeMaxThreads / 64,
+          [&](int w) { return tree_block_bytes(y, w); },
           [&](int w) {
-            if (!layered) return 0;
-            x.waves_per_block = w;
-            return greedy ? tree_greedy_blocks_per_cu(x) : tree_layers_blocks_per_cu(x);
+            y.waves_per_block = w;
+            return k == kTreeRank     ? tree_rank_blocks_per_cu(y)
+                   : k == kTreeGreedy ? tree_greedy_blocks_per_cu(y)
+                   : k == kTreeLayers ? tree_layers_blocks_per_cu(y)
+                                      : 0;
           });
-      x.waves_per_block = sh.waves;
+      y.waves_per_block = sh.waves;
       const int64_t want = (n + sh.waves - 1) / sh.waves;
       const int tgrid =
           (int)std::min<int64_t>(want, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
-      if (!layered) return launch_tree(x, tgrid, s);
-      return greedy ? launch_tree_greedy(x, tgrid, s) : launch_tree_layers(x, tgrid, s);
-    };
-    // The static order on the ranked kernel, when the plan's path lengths
-    // have exact short codes: Allgather, explicit multicast and the
-    // Allgather phase of an Allreduce (contiguous transfers included), and
-    // the ReduceScatter (alone or as an Allreduce's first phase) when every
-    // route hop has a reverse link of equal cost and there is no contiguity
-    TreeArgs ra = a;
-    const bool ranked = !greedy && t->rank_img &&
-                        tree_rank_layout(*p, ra) > 0 && tree_block_bytes(ra, 1) <= t->max_lds;
-    ra.rank_img = (const uint4 *)t->rank_img;
-    const bool ranked_rs = ranked && p->rank_rs_ok;
-    auto launch_ranked = [&](TreeArgs &x) {
-      const LaunchShape sh = launch_shape(
-          p, t, x.reduce ? kShapeRankReduce : kShapeRank, tree_rank_max_waves(x),
-          [&](int w) { return tree_block_bytes(x, w); },
-          [&](int w) {
-            x.waves_per_block = w;
-            return tree_rank_blocks_per_cu(x);
-          });
-      x.waves_per_block = sh.waves;
-      const int64_t want = (n + sh.waves - 1) / sh.waves;
-      const int tgrid =
-          (int)std::min<int64_t>(want, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
-      return launch_tree_rank(x, tgrid, s);
-    };
-    if (kind == TACCL_ALLREDUCE) {
-      // ReduceScatter on the first priority row, then Allgather on the
-      // second, adding its makespan (same stream, so in order)
-      a.reduce = 1;
-      a.accumulate = 0;
-      if (ranked_rs) {
-        TreeArgs r = ra;
-        r.reduce = 1;
-        r.accumulate = 0;
-        e = launch_ranked(r);
-      } else {
-        e = launch(a);
-      }
-      if (e == hipSuccess) {
-        TreeArgs b = ranked ? ra : a;
-        b.reduce = 0;
-        b.accumulate = 1;
-        b.prio = d_prio + (size_t)p->coll.C * p->topo.V;
-        e = ranked ? launch_ranked(b) : launch(b);
-      }
-    } else if (kind == TACCL_REDUCESCATTER ? ranked_rs : ranked) {
-      ra.reduce = kind == TACCL_REDUCESCATTER;
-      ra.accumulate = 0;
-      e = launch_ranked(ra);
-    } else {
-      a.reduce = kind == TACCL_REDUCESCATTER;
-      a.accumulate = 0;
-      e = launch(a);
+      e = k == kTreeRank     ? launch_tree_rank(y, tgrid, s)
+          : k == kTreeGreedy ? launch_tree_greedy(y, tgrid, s)
+          : k == kTreeLayers ? launch_tree_layers(y, tgrid, s)
+                             : launch_tree(y, tgrid, s);
     }
   }
   if (e != hipSuccess) return hip_fail(e, "kernel launch");

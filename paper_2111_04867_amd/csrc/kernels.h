@@ -220,14 +220,22 @@ constexpr int kPathThreads = 256;
 constexpr int kPathPortThreads = 1024;  // LDS-record kernel on switch-port plans
 constexpr int kPathFastThreads = 1024;  // largest block of the register-resident kernel
 
+// The kernel that evaluates a plan, or one phase of an Allreduce, on a device
+// whose blocks may use max_lds bytes of LDS: one rule for the launch and for
+// what the plan reports. Fills the chosen kernel's layout; kNoKernel: no
+// kernel takes the plan there (the layout that did not fit is left in place).
+// reduce: the ReduceScatter phase; route_words: the routes can be read as
+// aligned words.
+Kernel tree_select(const taccl_plan &p, bool reduce, bool route_words, int max_lds, TreeArgs &a);
+Kernel path_select(const taccl_plan &p, int max_lds, PathArgs &a, PathGreedyArgs &g, PortsArgs &t);
+
 // Fill the LDS layout; returns the bytes needed by a one-wavefront block.
 int32_t tree_layout(const taccl_plan &p, TreeArgs &a);
 // The same for the general variant (ReduceScatter, contiguous transfers and
 // greedy orders on plans outside the layered kernel's limits).
 int32_t tree_any_layout(const taccl_plan &p, TreeArgs &a);
 int32_t tree_block_bytes(const TreeArgs &a, int waves);
-// Ranked multicast kernel (static orders, no contiguity, trees forwards):
-// fills the layout and returns the bytes of a one-wavefront block, or 0
+// Ranked multicast kernel (static orders): fills the layout and returns the bytes of a one-wavefront block, or 0
 // when the plan does not meet its conditions.
 int32_t tree_rank_layout(const taccl_plan &p, TreeArgs &a);
 // the ranked kernel's shared LDS tables as one image (its first o_wave

@@ -909,6 +909,88 @@ static taccl_status_t build_layout(taccl_plan *p) {
   return TACCL_OK;
 }
 
+Kernel tree_select(const taccl_plan &p, bool reduce, bool route_words, int max_lds, TreeArgs &a) {
+  auto fits = [&](int32_t bytes) { return bytes > 0 && bytes <= max_lds; };
+  if (p.greedy) {
+    if (fits(tree_greedy_layout(p, a))) return kTreeGreedy;
+  } else {
+    // the ranked kernel takes plans whose path lengths have exact short
+    // codes; the ReduceScatter too when every route hop has a reverse link of
+    // equal cost and there is no contiguity
+    if (!p.rank_img.empty() && (!reduce || p.rank_rs_ok) && fits(tree_rank_layout(p, a)))
+      return kTreeRank;
+    // the layered kernel needs whole route words and priorities in registers
+    if (route_words && fits(tree_layers_layout(p, a))) return kTreeLayers;
+  }
+  // plans outside their limits: the general kernel, whose variant with
+  // reductions, contiguity and greedy orders keeps more state
+  const int kind = p.coll.kind;
+  a.any = kind == TACCL_REDUCESCATTER || kind == TACCL_ALLREDUCE || p.contig || p.greedy;
+  return fits(a.any ? tree_any_layout(p, a) : tree_layout(p, a)) ? kTree : kNoKernel;
+}
+
+Kernel path_select(const taccl_plan &p, int max_lds, PathArgs &a, PathGreedyArgs &g, PortsArgs &t) {
+  if (p.greedy) {
+    // one wavefront per candidate while its lists fit, else one block
+    const int32_t wave = path_greedy_layout(p, g);
+    if (wave > 0 && wave <= max_lds) return kPathGreedy;
+    const int32_t block = path_greedy_block_layout(p, g);
+    return block > 0 && block <= max_lds ? kPathGreedyBlock : kNoKernel;
+  }
+  if (p.ports && !path_ports_supported(p, max_lds)) {
+    path_layout(p, a);
+    return kNoKernel;
+  }
+  const int32_t ports = p.ports ? path_ports_layout(p, t) : 0;
+  if (ports > 0 && ports <= max_lds) return kPathPorts;
+  if (p.path_fast && path_fast_cpt(p) && path_fast_layout(p, a) <= max_lds) return kPathFast;
+  return path_layout(p, a) <= max_lds ? kPath : kNoKernel;
+}
+
+namespace {
+
+const char *kernel_name(Kernel k) {
+  switch (k) {
+    case kTree: return "tree_eval";
+    case kTreeLayers: return "tree_layers";
+    case kTreeGreedy: return "tree_greedy";
+    case kTreeRank: return "tree_rank";
+    case kPath: return "path_eval";
+    case kPathFast: return "path_eval_fast";
+    case kPathPorts: return "path_eval_ports";
+    case kPathGreedy: return "path_greedy";
+    case kPathGreedyBlock: return "path_greedy_block";
+    default: return "none";
+  }
+}
+
+// the kernels a plan runs on (routes read as words), and the LDS of one
+// block of theirs (of one wavefront, where blocks hold several)
+void report_kernels(taccl_plan *p) {
+  if (p->coll.kind == TACCL_ALLTOALL) {
+    PathArgs a{};
+    PathGreedyArgs g{};
+    PortsArgs t{};
+    const Kernel k = path_select(*p, kLdsBytes, a, g, t);
+    p->kernels = kernel_name(k);
+    p->lds_bytes = p->greedy ? (k == kPathGreedy ? g.o_wave + g.wave_bytes : g.block_bytes)
+                   : k == kPathPorts ? t.lds_bytes
+                                     : a.lds_bytes;
+    return;
+  }
+  const int kind = p->coll.kind;
+  for (int reduce = 1; reduce >= 0; reduce--) {
+    if (reduce ? kind != TACCL_REDUCESCATTER && kind != TACCL_ALLREDUCE
+               : kind == TACCL_REDUCESCATTER)
+      continue;
+    TreeArgs a{};
+    const Kernel k = tree_select(*p, reduce, p->route_stride % 4 == 0, kLdsBytes, a);
+    p->kernels += (p->kernels.empty() ? "" : "+") + std::string(kernel_name(k));
+    p->lds_bytes = std::max(p->lds_bytes, tree_block_bytes(a, 1));
+  }
+}
+
+}  // namespace
 }  // namespace taccl
 
 using namespace taccl;
@@ -1130,29 +1212,7 @@ taccl_status_t taccl_sketch_apply(taccl_topology_t topo, taccl_collective_t coll
     p->rank_img = tree_rank_image(*p);
     p->rank_rs_ok = tree_rank_reverse_ok(*p);
   }
-  // on-chip bytes of one block (of one wavefront, where blocks hold
-  // several) of the kernel the plan runs on, as the launch picks it
-  if (coll->kind == TACCL_ALLTOALL) {
-    PathArgs a{};
-    PathGreedyArgs g{};
-    PortsArgs t{};
-    const int32_t ports = path_ports_layout(*p, t);
-    if (ports > 0 && ports <= kLdsBytes && path_ports_supported(*p, kLdsBytes))
-      p->path_lds = ports;
-    else if (p->greedy)
-      p->path_lds = path_greedy_layout(*p, g) > 0 ? g.o_wave + g.wave_bytes
-                                                  : path_greedy_block_layout(*p, g);
-    else
-      p->path_lds =
-          (p->path_fast && path_fast_cpt(*p)) ? path_fast_layout(*p, a) : path_layout(*p, a);
-  } else {
-    TreeArgs a{};
-    const bool any = coll->kind == TACCL_REDUCESCATTER || coll->kind == TACCL_ALLREDUCE ||
-                     p->contig || p->greedy;
-    const int32_t layered =
-        p->greedy == 2 ? 0 : (p->greedy ? tree_greedy_layout(*p, a) : tree_layers_layout(*p, a));
-    p->tree_lds = layered > 0 ? layered : any ? tree_any_layout(*p, a) : tree_layout(*p, a);
-  }
+  report_kernels(p);
   *out = guard.release();
   clear_error();
   return TACCL_OK;
@@ -1175,9 +1235,11 @@ taccl_status_t taccl_plan_info(taccl_plan_t p, taccl_plan_info_t *o) {
   o->max_sends = p->max_sends;
   o->bytes_per_candidate = (uint64_t)p->route_stride + 4ull * p->prio_stride + 5ull;
   o->num_classes = p->ncls;
-  o->lds_bytes = p->coll.kind == TACCL_ALLTOALL ? p->path_lds : p->tree_lds;
+  o->lds_bytes = p->lds_bytes;
   return TACCL_OK;
 }
+
+const char *taccl_plan_kernels(taccl_plan_t p) { return p ? p->kernels.c_str() : ""; }
 
 taccl_status_t taccl_plan_route_options(taccl_plan_t p, int32_t *options) {
   if (!p || !options) return fail(TACCL_ERR_INVALID_ARGUMENT, "null plan or options");

@@ -50,10 +50,9 @@ namespace taccl {
 struct LaunchShape {
   int waves = 0, per_cu = 0;
 };
-// the kernels a plan may launch, each with a shape of its own
-enum ShapeOf { kShapeTree, kShapeTreeReduce, kShapeLayers, kShapeLayersReduce, kShapeRank,
-               kShapeRankReduce, kShapePathGreedy, kShapePathGreedyBlock, kShapePathFast,
-               kShapePathPorts,               kNumShapes };
+// the evaluation kernels
+enum Kernel { kNoKernel, kTree, kTreeLayers, kTreeGreedy, kTreeRank, kPath, kPathFast, kPathPorts,
+              kPathGreedy, kPathGreedyBlock, kNumKernels };
 
 // Device copies of the read-only plan tables (one set per device).
 struct DeviceTables {
@@ -90,7 +89,7 @@ struct DeviceTables {
   // Depends on the plan and the device alone, so it is worked out on first
   // use and kept (under the plan's mutex): the runtime's occupancy query for
   // every block size cost 2-3 us on each call
-  LaunchShape shape[kNumShapes];
+  LaunchShape shape[kNumKernels][2];  // [1]: the ReduceScatter variant
   int max_lds = 0;  // bytes of LDS a block may use on this device
   int lds_per_cu = 0;
   int num_cus = 0;
@@ -214,8 +213,9 @@ struct taccl_plan {
   std::vector<uint32_t> cn_rec, cn_chunk;
   int32_t conn_cells = 0;
 
-  // launch shape
-  int32_t tree_lds = 0, path_lds = 0;
+  // the kernels that evaluate the plan and the LDS of one block of theirs
+  std::string kernels;
+  int32_t lds_bytes = 0;
 
   std::mutex mu;
   std::map<int, taccl::DeviceTables> dev;

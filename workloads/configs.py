@@ -373,6 +373,28 @@ def two_node_full(P_per, kind, chunks_per_rank=1, k=3, chunk_bytes=64 * KIB, con
                     contiguity=contiguity)
 
 
+def cubemesh_nodes_ag(nodes, chunks_per_rank=1, k=3, chunk_bytes=256 * KIB):
+    """`nodes` 8-rank cube-meshes, IB both ways between ranks 0 and 4 of every
+    two, Allgather over the k shortest paths that cross nodes once at most."""
+    V = P = 8 * nodes
+    edges = []
+    for n in range(nodes):
+        edges += cube_mesh_edges(8 * n, NVLINK_ALPHA, NDV2_NVLINK_BETA)
+    relays = [8 * n + r for n in range(nodes) for r in (0, 4)]
+    edges += [(s, d, IB_ALPHA, IB_BETA) for s in relays for d in relays if s // 8 != d // 8]
+    row_ptr, col, a, b = csr_from_edges(V, edges)
+    relay = np.zeros(V, dtype=np.uint8)
+    relay[relays] = 1
+    return Workload(f"cubemesh{nodes}x8_ag", V, P, row_ptr, col, a, b,
+                    np.array([r // 8 for r in range(V)], dtype=np.int32), ALLGATHER,
+                    chunks_per_rank, chunk_bytes, KSHORTEST, k=k, max_cross=1, relay=relay)
+
+
+def broadcast(base, chunks):
+    """`chunks` chunks from rank 0 to every rank on the topology of `base`."""
+    return explicit_multicast(base, [0] * chunks, [list(range(base.P))] * chunks)
+
+
 def two_node_rings_a2a(P_per, chunk_bytes=64 * KIB, contiguity=1):
     """Two nodes whose ranks form a one-way ring, IB between rank i of one
     node and rank i of the other: Alltoall paths run up to 2*P_per - 1 links."""
