@@ -1567,7 +1567,9 @@ __global__ __launch_bounds__(kTreeMaxThreads) void path_greedy_kernel(PathGreedy
 // for the sends out of the destination, the ReduceScatter for the send that
 // carries the partial on), and the real times come from the orders it
 // leaves (greedy_real_times).
-template <int J, int PW, bool kRS>
+// kEntLds: the entering-link table (P * V * P * K bytes) is copied to LDS;
+// otherwise it stays in global memory, where the L2 holds it.
+template <int J, int PW, bool kRS, bool kEntLds>
 __global__ __launch_bounds__(kTreeMaxThreads) void tree_greedy_kernel(TreeArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int C = a.C, V = a.V, E = a.E;
@@ -1577,7 +1579,8 @@ __global__ __launch_bounds__(kTreeMaxThreads) void tree_greedy_kernel(TreeArgs a
   uint8_t *s_src = lds + a.o_src;
   uint8_t *s_own = lds + a.o_own;
   uint64_t *s_post = (uint64_t *)(lds + a.o_post);
-  uint8_t *s_ent = lds + a.o_ent;  // entering link per (o, v, d, k)
+  // entering link per (o, v, d, k)
+  const uint8_t *s_ent = kEntLds ? (const uint8_t *)(lds + a.o_ent) : a.ent;
   uint32_t *s_opt = (uint32_t *)(lds + a.o_opt);
   uint16_t *s_rev = (uint16_t *)(lds + a.o_rev);
   uint8_t *s_dst = lds + a.o_ldst;
@@ -1591,8 +1594,9 @@ __global__ __launch_bounds__(kTreeMaxThreads) void tree_greedy_kernel(TreeArgs a
   }
   // (both tables' bytes are padded to whole 16-byte groups in LDS and in
   // global memory)
-  for (int r = threadIdx.x; r < (a.P * V * a.P * a.K + 15) / 16; r += blockDim.x)
-    ((uint4 *)s_ent)[r] = ((const uint4 *)a.ent)[r];
+  if (kEntLds)
+    for (int r = threadIdx.x; r < (a.P * V * a.P * a.K + 15) / 16; r += blockDim.x)
+      ((uint4 *)(lds + a.o_ent))[r] = ((const uint4 *)a.ent)[r];
   for (int j = threadIdx.x; j < (a.P * V * PW + 3) / 4; j += blockDim.x)
     ((uint4 *)s_opt)[j] = ((const uint4 *)a.topt)[j];
   for (int j = threadIdx.x; j < C; j += blockDim.x) {
@@ -2008,18 +2012,15 @@ int32_t tree_greedy_layout(const taccl_plan &p, TreeArgs &a) {
   }
   if (cmin == 0 || (uint64_t)(V - 1) * cmax >= (1ull << 32)) return 0;
   a.cmin = cmin;
-  // shared tables: entering links and option bytes in place of the
-  // fixed-stride records
+  // shared tables: option bytes, and entering links where they are kept in
+  // LDS, in place of the fixed-stride records
   int32_t off = a.o_rec;
-  a.o_ent = off;
-  off = align16(off + P * V * P * K);
   a.o_opt = off;
   off = align16(off + 4 * P * V * pw);
   a.o_rev = off;
   off = align16(off + 2 * E);
   a.o_ldst = off;
   off = align16(off + E);
-  a.o_wave = off;
   const int32_t S = std::max<int64_t>(std::min<int64_t>(p.max_sends, CV), 1);
   int32_t w = 0;
   auto wtake = [&](int32_t bytes) {
@@ -2045,28 +2046,47 @@ int32_t tree_greedy_layout(const taccl_plan &p, TreeArgs &a) {
   a.w_anc = a.w_dist + align16(4 * CV);
   a.w_glist = u;
   a.wave_bytes = std::max(a.w_anc + a.pj_rounds * align16(2 * CV), u + align16(16 * S));
+  // The entering links' place. Up to 256 slots the registers admit 12
+  // wavefronts per CU or more, and the table in LDS costs some of them; past
+  // that they admit 8. There, up to 16 ranks, the table is read from LDS
+  // while 8 wavefronts still fit beside it: 20007 Allgathers on two 8-rank
+  // meshes with 2, 4 and 8 options took 662, 570 and 611 us with it in global
+  // memory, 639, 550 and 591 us from LDS. With 24 ranks global memory is the
+  // faster place whatever fits (20000 broadcasts of 20 chunks, 2 options:
+  // 1094 against 1118 us), and with large tables it is what keeps wavefronts
+  // resident (4000 broadcasts of 16 chunks on 32 ranks, 3 options: 719 us
+  // with 2 wavefronts per CU, 224 us with 8).
+  const int32_t ent = align16(P * V * P * K);
+  a.ent_lds = CV > 256 && pw <= 4 && resident_waves(off + ent, a.wave_bytes, 8) >= 8;
+  a.o_ent = off;
+  if (a.ent_lds) off += ent;
+  a.o_wave = off;
   return a.o_wave + a.wave_bytes;
 }
 
-template <int J, bool kR>
+// the table in LDS is only compiled for the plans the rule above gives it
+template <int J, bool kR, bool kEntLds>
 static const void *greedy_fn_j(int pw) {
   switch (pw) {
-    case 1: return (const void *)tree_greedy_kernel<J, 1, kR>;
-    case 2: return (const void *)tree_greedy_kernel<J, 2, kR>;
-    case 3: return (const void *)tree_greedy_kernel<J, 3, kR>;
-    case 4: return (const void *)tree_greedy_kernel<J, 4, kR>;
-    case 6: return (const void *)tree_greedy_kernel<J, 6, kR>;
-    default: return (const void *)tree_greedy_kernel<J, 8, kR>;
+    case 1: return (const void *)tree_greedy_kernel<J, 1, kR, kEntLds>;
+    case 2: return (const void *)tree_greedy_kernel<J, 2, kR, kEntLds>;
+    case 3: return (const void *)tree_greedy_kernel<J, 3, kR, kEntLds>;
+    case 4: return (const void *)tree_greedy_kernel<J, 4, kR, kEntLds>;
   }
+  if constexpr (!kEntLds) {
+    if (pw == 6) return (const void *)tree_greedy_kernel<J, 6, kR, false>;
+    if (pw == 8) return (const void *)tree_greedy_kernel<J, 8, kR, false>;
+  }
+  return nullptr;
 }
 
 template <bool kR>
 static const void *greedy_fn_r(const TreeArgs &a) {
   const int J = (a.C * a.V + 63) / 64, pw = rank_words(a.P);
-  if (J <= 1) return greedy_fn_j<1, kR>(pw);
-  if (J <= 2) return greedy_fn_j<2, kR>(pw);
-  if (J <= 4) return greedy_fn_j<4, kR>(pw);
-  return greedy_fn_j<8, kR>(pw);
+  if (J <= 1) return greedy_fn_j<1, kR, false>(pw);
+  if (J <= 2) return greedy_fn_j<2, kR, false>(pw);
+  if (J <= 4) return greedy_fn_j<4, kR, false>(pw);
+  return a.ent_lds ? greedy_fn_j<8, kR, true>(pw) : greedy_fn_j<8, kR, false>(pw);
 }
 
 static const void *greedy_fn(const TreeArgs &a) {
@@ -2123,7 +2143,8 @@ int tree_greedy_blocks_per_cu(const TreeArgs &a) {
 }
 
 hipError_t launch_tree_greedy(const TreeArgs &a, int grid, hipStream_t stream) {
-  if (a.P > 32 || a.C * a.V > 64 * kLayerMaxSlotsPerLane) return hipErrorInvalidValue;
+  if (a.P > 32 || a.C * a.V > 64 * kLayerMaxSlotsPerLane || !greedy_fn(a))
+    return hipErrorInvalidValue;
   const dim3 g(grid), b(64 * a.waves_per_block);
   void *args[] = {(void *)&a};
   return hipLaunchKernel(greedy_fn(a), g, b, args, tree_block_bytes(a, a.waves_per_block),

@@ -68,6 +68,7 @@ struct TreeArgs {
   int32_t qrange, rem_shift;
   const uint4 *rank_img;  // the block's shared LDS below o_wave, ready to copy
   const uint8_t *ent;
+  int32_t ent_lds;  // the entering-link table is in LDS
   int32_t o_rcost, o_ent, w_h, o_slot, opt_ostride, w_pj;
 };
 
@@ -200,6 +201,15 @@ typedef uint32_t __attribute__((aligned(1))) u32_any;
 inline int rank_words(int P) {
   const int w = (P + 3) / 4;
   return w == 5 ? 6 : w == 7 ? 8 : w;
+}
+
+// Wavefronts that a CU's LDS holds of a kernel with `shared` bytes per block
+// and `wave` bytes per wavefront, blocks of up to max_waves wavefronts
+inline int resident_waves(int64_t shared, int64_t wave, int max_waves) {
+  int most = 0;
+  for (int w = 1; w <= max_waves; w++)
+    most = std::max(most, std::min((int)(kLdsBytes / (shared + w * wave)) * w, 32));
+  return most;
 }
 
 constexpr int kConnMaxThreads = 256;

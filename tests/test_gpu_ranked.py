@@ -170,6 +170,37 @@ def test_greedy_slot_counts(P, C, order):
     check(order(broadcast(cf.full_ag(P, k=2) if P != 27 else ring(P), C)), n=33)
 
 
+def torus_broadcast(side, P, C, k):
+    """C chunks to the first P of side x side torus vertices, the others
+    switches: tables of P * P * side^2 * k bytes."""
+    V = side * side
+    edges = []
+    for v in range(V):
+        r, c = divmod(v, side)
+        for u in (r * side + (c + 1) % side, (r + 1) % side * side + c):
+            edges += [(v, u, 700, 46), (u, v, 700, 46)]
+    row_ptr, col, a, b = cf.csr_from_edges(V, edges)
+    return broadcast(cf.Workload(f"torus{side}_{P}", V, P, row_ptr, col, a, b, None, cf.ALLGATHER,
+                                 1, 65536, cf.KSHORTEST, k=k), C)
+
+
+@pytest.mark.parametrize("order", [cf.with_greedy, cf.with_reverse_greedy],
+                         ids=["greedy", "reverse"])
+@pytest.mark.parametrize("make", [lambda: broadcast(cf.cubemesh_nodes_ag(4, k=4), 16),
+                                  lambda: broadcast(cf.cubemesh_nodes_ag(3, k=8), 20),
+                                  lambda: broadcast(cf.cubemesh_nodes_ag(3, k=3), 5),
+                                  lambda: torus_broadcast(6, 16, 14, 8),
+                                  lambda: torus_broadcast(4, 16, 32, 8)],
+                         ids=["4x8", "3x8", "3x8_small", "torus6", "torus4"])
+def test_greedy_entering_links(make, order):
+    """Entering links in global memory, past 256 slots (24 and 32 ranks; 16
+    whose table would leave few wavefronts) and below, and in LDS."""
+    w = order(make())
+    from paper_2111_04867_amd.binding import Plan
+    assert Plan.from_workload(w).kernels == "tree_greedy"
+    check(w, n=33)
+
+
 @pytest.mark.parametrize("order", [cf.with_greedy, cf.with_reverse_greedy],
                          ids=["greedy", "reverse"])
 @pytest.mark.parametrize("per,cpr,kib", [(3, 1, 17), (5, 1, 333), (6, 2, 4)])

@@ -45,6 +45,19 @@ def test_kernel_of_a_plan(w, kernels):
     assert Plan.from_workload(w).kernels == kernels
 
 
+# plans whose entering-link table (P * V * P * K bytes) takes more LDS than a
+# block has, or would leave a CU few of the 8 wavefronts its registers admit:
+# at most 48 KB for a block of one of them, shared tables of 34 KB with it
+@pytest.mark.parametrize("nodes,chunks,k", [(4, 16, 2), (4, 16, 3), (4, 16, 4), (4, 16, 8),
+                                            (3, 20, 8), (3, 8, 4), (3, 21, 3)])
+@pytest.mark.parametrize("order", [cf.with_greedy, cf.with_reverse_greedy],
+                         ids=["greedy", "reverse"])
+def test_greedy_keeps_large_tables_out_of_lds(nodes, chunks, k, order):
+    p = Plan.from_workload(order(mesh_broadcast(nodes, chunks, k)))
+    assert p.kernels == "tree_greedy"
+    assert p.info["lds_bytes"] <= 48 * 1024
+
+
 @pytest.mark.parametrize("order", [lambda w: w, cf.with_greedy, cf.with_reverse_greedy,
                                    lambda w: cf.as_reduction(w, cf.ALLREDUCE)],
                          ids=["static", "greedy", "reverse", "allreduce"])
