@@ -113,31 +113,39 @@ taccl_status_t ensure_device(taccl_plan *p, DeviceTables **out) {
   return TACCL_OK;
 }
 
-// The launch shape of one of the plan's kernels on this device: the block
-// size (1 to max_waves wavefronts) with the most resident wavefronts per CU,
-// by LDS, the 32 wavefronts of a CU and the runtime's occupancy query
-// (per_cu(waves); 0 if it fails). bytes(waves): LDS of a block.
-template <class Bytes, class PerCu>
-LaunchShape launch_shape(taccl_plan *p, DeviceTables *t, Kernel kernel, bool reduce, int max_waves,
-                         Bytes bytes, PerCu per_cu) {
+// Resident blocks of `threads` threads per CU by registers, `otherwise` if the
+// query fails
+int blocks_by_registers(const void *fn, int threads, int otherwise) {
+  int nb = 0;
+  if (!fn || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, threads, 0) != hipSuccess ||
+      nb < 1)
+    return otherwise;
+  return nb;
+}
+
+// The launch shape of a kernel whose blocks hold wavefronts of `wave` bytes
+// of LDS beside `shared` bytes, up to max_waves of them. fn null: a kernel
+// whose registers don't bound it.
+LaunchShape wave_shape(taccl_plan *p, DeviceTables *t, Kernel kernel, bool reduce, const void *fn,
+                       int shared, int wave, int max_waves) {
   std::lock_guard<std::mutex> lock(p->mu);
   LaunchShape &s = t->shape[kernel][reduce];
-  if (s.waves) return s;
-  LaunchShape best{1, 1};
-  int best_res = 0;
-  for (int w = 1; w <= max_waves; w++) {
-    const int b = bytes(w);
-    if (b > t->max_lds) break;
-    int bpc = std::min(t->lds_per_cu / b, 32 / w);
-    const int nb = per_cu(w);
-    if (nb > 0) bpc = std::min(bpc, nb);
-    const int res = std::min(bpc * w, 32);
-    if (res > best_res) {
-      best_res = res;
-      best = LaunchShape{w, bpc};
-    }
-  }
-  return s = best;
+  if (!s.waves)
+    // a block of four wavefronts has one on every SIMD
+    s = resident_shape(shared, wave, max_waves, std::min(blocks_by_registers(fn, 256, 8), 8),
+                       t->max_lds, t->lds_per_cu);
+  return s;
+}
+
+// The same for a kernel of one block size: its resident blocks per CU.
+LaunchShape block_shape(taccl_plan *p, DeviceTables *t, Kernel kernel, const void *fn, int threads,
+                        int bytes) {
+  std::lock_guard<std::mutex> lock(p->mu);
+  LaunchShape &s = t->shape[kernel][0];
+  if (!s.waves)
+    s = LaunchShape{1, std::max(1, std::min(blocks_by_lds(bytes, t->lds_per_cu),
+                                            blocks_by_registers(fn, threads, 1)))};
+  return s;
 }
 
 }  // namespace
@@ -214,26 +222,18 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     g.n = n;
     if (kernel == kPathGreedyBlock) {
       // the block kernel has one size: only its resident blocks are asked for
-      const LaunchShape sh = launch_shape(
-          p, t, kernel, false, 1, [&](int) { return g.block_bytes; },
-          [&](int) { return path_greedy_block_per_cu(g); });
+      const LaunchShape sh = block_shape(p, t, kernel, path_greedy_block_fn(g), kGreedyBlockThreads,
+                                         g.block_bytes);
       const int bgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
       e = launch_path_greedy_block(g, bgrid, s);
       if (e != hipSuccess) return hip_fail(e, "kernel launch");
       return TACCL_OK;
     }
     // wavefronts per block: most resident wavefronts per CU
-    const LaunchShape sh = launch_shape(
-        p, t, kernel, false, kTreeMaxThreads / 64,
-        [&](int w) { return g.o_wave + w * g.wave_bytes; },
-        [&](int w) {
-          g.waves_per_block = w;
-          return path_greedy_blocks_per_cu(g);
-        });
+    const LaunchShape sh = wave_shape(p, t, kernel, false, path_greedy_fn(), g.o_wave, g.wave_bytes,
+                                      kTreeMaxThreads / 64);
     g.waves_per_block = sh.waves;
-    const int64_t want = (n + sh.waves - 1) / sh.waves;
-    const int ggrid = (int)std::min<int64_t>(want, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
-    e = launch_path_greedy(g, ggrid, s);
+    e = launch_path_greedy(g, wave_grid(sh, n, t->num_cus, false), s);
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return TACCL_OK;
   }
@@ -257,9 +257,7 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     pa.makespan = d_makespan;
     pa.valid = d_valid;
     pa.n = n;
-    const LaunchShape sh = launch_shape(
-        p, t, kernel, false, 1, [&](int) { return pa.lds_bytes; },
-        [&](int) { return path_ports_blocks_per_cu(pa); });
+    const LaunchShape sh = block_shape(p, t, kernel, path_ports_fn(pa), pa.nt, pa.lds_bytes);
     const int pgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
     e = launch_path_ports(pa, pgrid, s);
   } else if (p->coll.kind == TACCL_ALLTOALL) {
@@ -307,9 +305,8 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     a.cbkt = t->cbkt;
     if (kernel == kPathFast) {
       const int cpt = path_fast_cpt(*p), nt = path_fast_threads(*p);
-      const LaunchShape sh = launch_shape(
-          p, t, kernel, false, 1, [&](int) { return a.lds_bytes; },
-          [&](int) { return path_fast_blocks_per_cu(a, cpt, nt); });
+      const LaunchShape sh =
+          block_shape(p, t, kernel, path_fast_fn(a, cpt, nt), nt, a.lds_bytes);
       const int fgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
       e = launch_path_fast(a, cpt, nt, fgrid, s);
     } else {
@@ -368,22 +365,25 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     for (int i = 0; i < phases && e == hipSuccess; i++) {
       TreeArgs &y = phase[i];
       const Kernel k = kernels[i];
-      // wavefronts per block: most resident wavefronts per CU (LDS, and but
-      // for the general kernel registers too, by the runtime's occupancy query)
-      const LaunchShape sh = launch_shape(
-          p, t, k, y.reduce != 0, k == kTreeRank ? tree_rank_max_waves(y) : kTreeMaxThreads / 64,
-          [&](int w) { return tree_block_bytes(y, w); },
-          [&](int w) {
-            y.waves_per_block = w;
-            return k == kTreeRank     ? tree_rank_blocks_per_cu(y)
-                   : k == kTreeGreedy ? tree_greedy_blocks_per_cu(y)
-                   : k == kTreeLayers ? tree_layers_blocks_per_cu(y)
-                                      : 0;
-          });
+      const void *fn = k == kTreeRank     ? tree_rank_fn(y)
+                       : k == kTreeGreedy ? tree_greedy_fn(y)
+                       : k == kTreeLayers ? tree_layers_fn(y)
+                                          : nullptr;
+      const LaunchShape sh =
+          wave_shape(p, t, k, y.reduce != 0, fn, y.o_wave, y.wave_bytes,
+                     k == kTreeRank ? tree_rank_max_waves(y) : kTreeMaxThreads / 64);
       y.waves_per_block = sh.waves;
-      const int64_t want = (n + sh.waves - 1) / sh.waves;
-      const int tgrid =
-          (int)std::min<int64_t>(want, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
+      // The ranked kernel's candidates are dealt out over the blocks where a CU
+      // holds one of them, so that a batch which is no multiple of the resident
+      // wavefronts leaves every CU with as few as it can (20000 Allgathers on
+      // two 8-rank meshes 144 -> 129 us, 44 Allreduces on two nodes of 7 ranks
+      // 41.1 -> 30.4 us). With several blocks per CU they fill up block by
+      // block: dealt out, the last ones would all be on the SIMDs of the
+      // blocks' first wavefronts (20000 Allgathers on 10 ranks 35.1 -> 38.2 us).
+      const bool spread = k == kTreeRank && sh.per_cu == 1;
+      const int tgrid = wave_grid(sh, n, t->num_cus, spread);
+      y.first_block = spread ? 1 : sh.waves;
+      y.first_wave = spread ? tgrid : 1;
       e = k == kTreeRank     ? launch_tree_rank(y, tgrid, s)
           : k == kTreeGreedy ? launch_tree_greedy(y, tgrid, s)
           : k == kTreeLayers ? launch_tree_layers(y, tgrid, s)

@@ -445,13 +445,8 @@ int32_t path_greedy_block_layout(const taccl_plan &p, PathGreedyArgs &a) {
   return off;
 }
 
-int path_greedy_block_per_cu(const PathGreedyArgs &a) {
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, block_fn<kGreedyBlockThreads>(a),
-                                                   kGreedyBlockThreads, a.block_bytes) !=
-      hipSuccess)
-    return 0;
-  return nb;
+const void *path_greedy_block_fn(const PathGreedyArgs &a) {
+  return block_fn<kGreedyBlockThreads>(a);
 }
 
 hipError_t launch_path_greedy_block(const PathGreedyArgs &a, int grid, hipStream_t stream) {

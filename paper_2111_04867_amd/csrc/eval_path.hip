@@ -997,17 +997,10 @@ static const void *path_fast_fn_c(int cpt, int nt) {
   return nullptr;
 }
 
-static const void *path_fast_fn(const PathArgs &a, int cpt, int nt) {
+const void *path_fast_fn(const PathArgs &a, int cpt, int nt) {
   return a.contig ? path_fast_fn_c<true>(cpt, nt) : path_fast_fn_c<false>(cpt, nt);
 }
 
-int path_fast_blocks_per_cu(const PathArgs &a, int cpt, int nt) {
-  const void *fn = path_fast_fn(a, cpt, nt);
-  int nb = 0;
-  if (!fn || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, nt, a.lds_bytes) != hipSuccess)
-    return 0;
-  return nb;
-}
 
 hipError_t launch_path_fast(const PathArgs &a, int cpt, int nt, int grid, hipStream_t stream) {
   const void *fn = path_fast_fn(a, cpt, nt);

@@ -393,13 +393,7 @@ int32_t path_ports_layout(const taccl_plan &p, PortsArgs &a) {
   return off;
 }
 
-int path_ports_blocks_per_cu(const PortsArgs &a) {
-  const void *fn = ports_fn(a.cpt, a.nt);
-  int nb = 0;
-  if (!fn || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, a.nt, a.lds_bytes) != hipSuccess)
-    return 0;
-  return nb;
-}
+const void *path_ports_fn(const PortsArgs &a) { return ports_fn(a.cpt, a.nt); }
 
 hipError_t launch_path_ports(const PortsArgs &a, int grid, hipStream_t stream) {
   const void *fn = ports_fn(a.cpt, a.nt);

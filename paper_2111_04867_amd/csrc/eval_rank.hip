@@ -154,7 +154,7 @@ __global__ __launch_bounds__(rank_max_threads<J>()) void tree_rank_kernel(TreeAr
   };
 
   const int64_t stride = (int64_t)gridDim.x * a.waves_per_block;
-  const int64_t first = (int64_t)blockIdx.x * a.waves_per_block + wave;
+  const int64_t first = blockIdx.x * a.first_block + wave * a.first_wave;
   // A chunk's row of P route bytes takes PW words; with P below 4 PW a word
   // starts pad bytes earlier per chunk before it than its index says, and the
   // words that would reach past the candidate's row are read from the row's
@@ -876,14 +876,7 @@ bool tree_rank_reverse_ok(const taccl_plan &p) {
   return true;
 }
 
-int tree_rank_blocks_per_cu(const TreeArgs &a) {
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, rank_fn(a), 64 * a.waves_per_block,
-                                                   tree_block_bytes(a, a.waves_per_block)) !=
-      hipSuccess)
-    return 0;
-  return nb;
-}
+const void *tree_rank_fn(const TreeArgs &a) { return rank_fn(a); }
 
 int tree_rank_max_waves(const TreeArgs &a) {
   return (rank_slots_per_lane(a.C * a.V) <= 8 ? rank_max_threads<8>() : rank_max_threads<16>()) / 64;

@@ -1974,14 +1974,7 @@ static const void *layers_fn(const TreeArgs &a) {
   return a.contig ? layers_fn_c<true, false>(a) : layers_fn_c<false, false>(a);
 }
 
-int tree_layers_blocks_per_cu(const TreeArgs &a) {
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, layers_fn(a), 64 * a.waves_per_block,
-                                                   tree_block_bytes(a, a.waves_per_block)) !=
-      hipSuccess)
-    return 0;
-  return nb;
-}
+const void *tree_layers_fn(const TreeArgs &a) { return layers_fn(a); }
 
 hipError_t launch_tree_layers(const TreeArgs &a, int grid, hipStream_t stream) {
   const int pw = a.P / 4;
@@ -2057,7 +2050,7 @@ int32_t tree_greedy_layout(const taccl_plan &p, TreeArgs &a) {
   // resident (4000 broadcasts of 16 chunks on 32 ranks, 3 options: 719 us
   // with 2 wavefronts per CU, 224 us with 8).
   const int32_t ent = align16(P * V * P * K);
-  a.ent_lds = CV > 256 && pw <= 4 && resident_waves(off + ent, a.wave_bytes, 8) >= 8;
+  a.ent_lds = CV > 256 && pw <= 4 && resident_shape(off + ent, a.wave_bytes, 8, 2).resident() >= 8;
   a.o_ent = off;
   if (a.ent_lds) off += ent;
   a.o_wave = off;
@@ -2117,15 +2110,7 @@ int32_t path_greedy_layout(const taccl_plan &p, PathGreedyArgs &a) {
   return a.o_wave + a.wave_bytes;
 }
 
-int path_greedy_blocks_per_cu(const PathGreedyArgs &a) {
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void *)path_greedy_kernel,
-                                                   64 * a.waves_per_block,
-                                                   a.o_wave + a.waves_per_block * a.wave_bytes) !=
-      hipSuccess)
-    return 0;
-  return nb;
-}
+const void *path_greedy_fn() { return (const void *)path_greedy_kernel; }
 
 hipError_t launch_path_greedy(const PathGreedyArgs &a, int grid, hipStream_t stream) {
   void *args[] = {(void *)&a};
@@ -2133,14 +2118,7 @@ hipError_t launch_path_greedy(const PathGreedyArgs &a, int grid, hipStream_t str
                          args, a.o_wave + a.waves_per_block * a.wave_bytes, stream);
 }
 
-int tree_greedy_blocks_per_cu(const TreeArgs &a) {
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, greedy_fn(a), 64 * a.waves_per_block,
-                                                   tree_block_bytes(a, a.waves_per_block)) !=
-      hipSuccess)
-    return 0;
-  return nb;
-}
+const void *tree_greedy_fn(const TreeArgs &a) { return greedy_fn(a); }
 
 hipError_t launch_tree_greedy(const TreeArgs &a, int grid, hipStream_t stream) {
   if (a.P > 32 || a.C * a.V > 64 * kLayerMaxSlotsPerLane || !greedy_fn(a))

@@ -68,6 +68,9 @@ struct TreeArgs {
   int32_t qrange, rem_shift;
   const uint4 *rank_img;  // the block's shared LDS below o_wave, ready to copy
   const uint8_t *ent;
+  // first candidate of a wavefront: first_block per block + first_wave per
+  // wavefront of the block (ranked kernel)
+  uint32_t first_block, first_wave;
   int32_t ent_lds;  // the entering-link table is in LDS
   int32_t o_rcost, o_ent, w_h, o_slot, opt_ostride, w_pj;
 };
@@ -203,15 +206,6 @@ inline int rank_words(int P) {
   return w == 5 ? 6 : w == 7 ? 8 : w;
 }
 
-// Wavefronts that a CU's LDS holds of a kernel with `shared` bytes per block
-// and `wave` bytes per wavefront, blocks of up to max_waves wavefronts
-inline int resident_waves(int64_t shared, int64_t wave, int max_waves) {
-  int most = 0;
-  for (int w = 1; w <= max_waves; w++)
-    most = std::max(most, std::min((int)(kLdsBytes / (shared + w * wave)) * w, 32));
-  return most;
-}
-
 constexpr int kConnMaxThreads = 256;
 constexpr int kConnWaveThreads = 1024;
 // record tables up to this size are copied to LDS by every block
@@ -255,7 +249,7 @@ std::vector<uint8_t> tree_rank_image(const taccl_plan &p);
 // equal costs, no contiguity)
 bool tree_rank_reverse_ok(const taccl_plan &p);
 int tree_rank_max_waves(const TreeArgs &a);  // most wavefronts per block
-int tree_rank_blocks_per_cu(const TreeArgs &a);
+const void *tree_rank_fn(const TreeArgs &a);  // the kernel, for occupancy queries
 hipError_t launch_tree_rank(const TreeArgs &a, int grid, hipStream_t stream);
 // Layered multicast kernel: fills the layout and returns the bytes of a
 // one-wavefront block, or 0 when the plan does not meet its conditions.
@@ -264,12 +258,12 @@ int32_t tree_layers_layout(const taccl_plan &p, TreeArgs &a);
 // bytes of a one-wavefront block, or 0 when the plan does not fit it.
 int32_t tree_greedy_layout(const taccl_plan &p, TreeArgs &a);
 hipError_t launch_tree_greedy(const TreeArgs &a, int grid, hipStream_t stream);
-int tree_greedy_blocks_per_cu(const TreeArgs &a);
+const void *tree_greedy_fn(const TreeArgs &a);
 int32_t path_layout(const taccl_plan &p, PathArgs &a);
 int32_t path_fast_layout(const taccl_plan &p, PathArgs &a);
 int path_fast_cpt(const taccl_plan &p);      // chunks per thread, 0 = not eligible
 int path_fast_threads(const taccl_plan &p);  // threads per block: 256, 512 or 1024
-int path_fast_blocks_per_cu(const PathArgs &a, int cpt, int nt);
+const void *path_fast_fn(const PathArgs &a, int cpt, int nt);
 
 // a switch-port plan is within what the general kernel takes (the plans that
 // evaluation accepts, whichever kernel runs them)
@@ -277,14 +271,14 @@ bool path_ports_supported(const taccl_plan &p, int max_lds);
 // Alltoall with switch ports: fills the layout and returns the block's LDS
 // bytes, or 0 when the plan does not meet the kernel's conditions
 int32_t path_ports_layout(const taccl_plan &p, PortsArgs &a);
-int path_ports_blocks_per_cu(const PortsArgs &a);
+const void *path_ports_fn(const PortsArgs &a);
 hipError_t launch_path_ports(const PortsArgs &a, int grid, hipStream_t stream);
 
 hipError_t launch_tree(const TreeArgs &a, int grid, hipStream_t stream);
 // Alltoall greedy: fills the layout; returns the bytes of a one-wavefront
 // block, or 0 when the plan has more than 1024 send slots or 256 links
 int32_t path_greedy_layout(const taccl_plan &p, PathGreedyArgs &a);
-int path_greedy_blocks_per_cu(const PathGreedyArgs &a);
+const void *path_greedy_fn();
 hipError_t launch_path_greedy(const PathGreedyArgs &a, int grid, hipStream_t stream);
 // Alltoall greedy, one block per candidate (plans beyond the wavefront
 // kernel): fills the layout; returns the block's LDS bytes, or 0 when the
@@ -292,7 +286,7 @@ hipError_t launch_path_greedy(const PathGreedyArgs &a, int grid, hipStream_t str
 // a zero-cost link
 constexpr int kGreedyBlockThreads = 1024;
 int32_t path_greedy_block_layout(const taccl_plan &p, PathGreedyArgs &a);
-int path_greedy_block_per_cu(const PathGreedyArgs &a);
+const void *path_greedy_block_fn(const PathGreedyArgs &a);
 hipError_t launch_path_greedy_block(const PathGreedyArgs &a, int grid, hipStream_t stream);
 // connection count: LDS bytes of a block of `threads`, and the launch
 int32_t connections_lds_bytes(const ConnArgs &a, int threads);
@@ -302,8 +296,7 @@ hipError_t launch_connections(const ConnArgs &a, int threads, int grid, hipStrea
 int32_t connections_wave_lds_bytes(const ConnArgs &a, int waves);
 hipError_t launch_connections_wave(const ConnArgs &a, int waves, int grid, hipStream_t stream);
 hipError_t launch_tree_layers(const TreeArgs &a, int grid, hipStream_t stream);
-// resident blocks per CU of the layered kernel at a.waves_per_block
-int tree_layers_blocks_per_cu(const TreeArgs &a);
+const void *tree_layers_fn(const TreeArgs &a);
 hipError_t launch_path(const PathArgs &a, int grid, hipStream_t stream);
 hipError_t launch_path_fast(const PathArgs &a, int cpt, int nt, int grid, hipStream_t stream);
 

@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "shape.h"
 #include "taccl.h"
 
 namespace taccl {
@@ -19,8 +20,6 @@ constexpr int kFastMaxChunks = 4096;
 constexpr int kFastMaxBuckets = 16384;
 // the same for the switch-port kernel (both port orders' buckets together)
 constexpr int kPortsMaxBuckets = 12288;
-// LDS of a CU, and of the largest block
-constexpr int32_t kLdsBytes = 160 * 1024;
 // chunk table entry of a pair that has no route option at all
 constexpr uint32_t kNoRoute = 0x00FFFFFFu;
 
@@ -45,11 +44,6 @@ struct taccl_collective {
 
 namespace taccl {
 
-// A kernel's launch shape on one device: wavefronts per block and resident
-// blocks per CU (0: not yet computed).
-struct LaunchShape {
-  int waves = 0, per_cu = 0;
-};
 // the evaluation kernels
 enum Kernel { kNoKernel, kTree, kTreeLayers, kTreeGreedy, kTreeRank, kPath, kPathFast, kPathPorts,
               kPathGreedy, kPathGreedyBlock, kNumKernels };
@@ -88,7 +82,7 @@ struct DeviceTables {
   const uint32_t *cn_rec = nullptr, *cn_chunk = nullptr;
   // Depends on the plan and the device alone, so it is worked out on first
   // use and kept (under the plan's mutex): the runtime's occupancy query for
-  // every block size cost 2-3 us on each call
+  // every block size cost 2-3 us on each call (one query now, on the first)
   LaunchShape shape[kNumKernels][2];  // [1]: the ReduceScatter variant
   int max_lds = 0;  // bytes of LDS a block may use on this device
   int lds_per_cu = 0;
