@@ -133,7 +133,7 @@ LaunchShape wave_shape(taccl_plan *p, DeviceTables *t, Kernel kernel, bool reduc
   if (!s.waves)
     // a block of four wavefronts has one on every SIMD
     s = resident_shape(shared, wave, max_waves, std::min(blocks_by_registers(fn, 256, 8), 8),
-                       t->max_lds, t->lds_per_cu);
+                       kernel == kTreeRank, t->max_lds, t->lds_per_cu);
   return s;
 }
 

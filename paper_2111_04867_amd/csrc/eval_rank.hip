@@ -102,7 +102,9 @@ __device__ __forceinline__ uint32_t one_hot(uint32_t w, uint32_t j, const uint64
 // remaining length = reversed distance from v to the owner, travelled
 // length = longest reversed path from below up to v; a send is ready when
 // every send into v has finished)
-template <int J, int PW, bool kC, bool kR>
+// kEntLds: the entering-link table (P * V * P * K bytes) is in LDS; otherwise
+// in global memory, where the L2 holds it.
+template <int J, int PW, bool kC, bool kR, bool kEntLds>
 __global__ __launch_bounds__(rank_max_threads<J>()) void tree_rank_kernel(TreeArgs a) {
   static_assert(!(kC && kR), "contiguous transfers are not combined with ReduceScatter here");
   extern __shared__ __align__(16) unsigned char lds[];
@@ -118,11 +120,7 @@ __global__ __launch_bounds__(rank_max_threads<J>()) void tree_rank_kernel(TreeAr
   // owner, so that the 16 lanes of a row (one chunk, consecutive vertices)
   // read 16 banks and two owners fall on different halves
   uint32_t *s_opt = (uint32_t *)(lds + a.o_opt);
-  // entering link per (o, v, d, k). Past 8 slots per lane the table (P * V *
-  // P * K bytes: 41 KB at 24 ranks) stays in global memory, where the L2
-  // holds it: in LDS it left room for 2 to 6 wavefronts per CU, and those
-  // plans are bound by the wavefronts in flight
-  constexpr bool kEntLds = J <= 8;
+  // entering link per (o, v, d, k)
   const uint8_t *s_ent = kEntLds ? (const uint8_t *)(lds + a.o_ent) : a.ent;
   // per slot: entering-link table base | chunk's first slot << 20 | root <<
   // 30 | in the postcondition << 31, and option base | route word base << 16
@@ -232,9 +230,12 @@ __global__ __launch_bounds__(rank_max_threads<J>()) void tree_rank_kernel(TreeAr
     // an / acc: the slot's 2^k-th ancestor and the cost of the path up to it
     uint32_t pl[J], an[J], acc[J];
     uint32_t bad = 0, fault = 0;
+    // (four table reads on their way at once from global memory, where the
+    // registers allow it)
+    constexpr int G = J < 2 ? J : kEntLds || J % 4 || J == 8 ? 2 : 4;
+    static_assert(J % G == 0, "whole groups of slots");
 #pragma unroll
-    for (int g0 = 0; g0 < J; g0 += (J < 2 ? J : J <= 8 || J % 4 ? 2 : 4)) {
-      constexpr int G = J < 2 ? J : kEntLds || J % 4 ? 2 : 4;
+    for (int g0 = 0; g0 < J; g0 += G) {
       uint32_t slc[G], pos[G];
       uint2 si[G];
 #pragma unroll
@@ -680,41 +681,54 @@ int rank_slots_per_lane(int cv) {
   return j <= 2 ? std::max(j, 1) : j <= 4 ? 4 : j <= 6 ? 6 : j <= 8 ? 8 : j <= 10 ? 10 : j <= 12 ? 12 : j <= 14 ? 14 : 16;
 }
 
+// The plans with the entering-link table in LDS (see tree_rank_layout): up to
+// 8 ranks, and at 6 and 8 slots per lane small tables of more ranks
 template <int J, bool kC, bool kR>
-const void *rank_fn_jc(int pw) {
-  switch (pw) {
-    case 3: return (const void *)tree_rank_kernel<J, 3, kC, kR>;
-    case 4: return (const void *)tree_rank_kernel<J, 4, kC, kR>;
-    case 6: return (const void *)tree_rank_kernel<J, 6, kC, kR>;
-    case 8: return (const void *)tree_rank_kernel<J, 8, kC, kR>;
-  }
+const void *rank_fn_jc(int pw, bool ent_lds) {
   if constexpr (J <= 8) {
-    if (pw == 1) return (const void *)tree_rank_kernel<J, 1, kC, kR>;
-    if (pw == 2) return (const void *)tree_rank_kernel<J, 2, kC, kR>;
+    if (ent_lds) {
+      if (pw == 1) return (const void *)tree_rank_kernel<J, 1, kC, kR, true>;
+      if (pw == 2) return (const void *)tree_rank_kernel<J, 2, kC, kR, true>;
+      if constexpr (J > 4) {
+        if (pw == 3) return (const void *)tree_rank_kernel<J, 3, kC, kR, true>;
+        if (pw == 4) return (const void *)tree_rank_kernel<J, 4, kC, kR, true>;
+        if (pw == 6) return (const void *)tree_rank_kernel<J, 6, kC, kR, true>;
+        if (pw == 8) return (const void *)tree_rank_kernel<J, 8, kC, kR, true>;
+      }
+      return nullptr;
+    }
+  }
+  if (ent_lds) return nullptr;
+  switch (pw) {
+    case 3: return (const void *)tree_rank_kernel<J, 3, kC, kR, false>;
+    case 4: return (const void *)tree_rank_kernel<J, 4, kC, kR, false>;
+    case 6: return (const void *)tree_rank_kernel<J, 6, kC, kR, false>;
+    case 8: return (const void *)tree_rank_kernel<J, 8, kC, kR, false>;
   }
   return nullptr;
 }
 
 // ReduceScatter never runs with contiguous transfers here
 template <int J>
-const void *rank_fn_j(int pw, bool contig, bool reduce) {
-  if (reduce) return rank_fn_jc<J, false, true>(pw);
-  return contig ? rank_fn_jc<J, true, false>(pw) : rank_fn_jc<J, false, false>(pw);
+const void *rank_fn_j(int pw, bool contig, bool reduce, bool ent_lds) {
+  if (reduce) return rank_fn_jc<J, false, true>(pw, ent_lds);
+  return contig ? rank_fn_jc<J, true, false>(pw, ent_lds)
+                : rank_fn_jc<J, false, false>(pw, ent_lds);
 }
 
 const void *rank_fn(const TreeArgs &a) {
   const int pw = rank_words(a.P);
-  const bool c = a.contig != 0, r = a.reduce != 0;
+  const bool c = a.contig != 0, r = a.reduce != 0, e = a.ent_lds != 0;
   switch (rank_slots_per_lane(a.C * a.V)) {
-    case 1: return rank_fn_j<1>(pw, c, r);
-    case 2: return rank_fn_j<2>(pw, c, r);
-    case 4: return rank_fn_j<4>(pw, c, r);
-    case 6: return rank_fn_j<6>(pw, c, r);
-    case 8: return rank_fn_j<8>(pw, c, r);
-    case 10: return rank_fn_j<10>(pw, c, r);
-    case 12: return rank_fn_j<12>(pw, c, r);
-    case 14: return rank_fn_j<14>(pw, c, r);
-    default: return rank_fn_j<16>(pw, c, r);
+    case 1: return rank_fn_j<1>(pw, c, r, e);
+    case 2: return rank_fn_j<2>(pw, c, r, e);
+    case 4: return rank_fn_j<4>(pw, c, r, e);
+    case 6: return rank_fn_j<6>(pw, c, r, e);
+    case 8: return rank_fn_j<8>(pw, c, r, e);
+    case 10: return rank_fn_j<10>(pw, c, r, e);
+    case 12: return rank_fn_j<12>(pw, c, r, e);
+    case 14: return rank_fn_j<14>(pw, c, r, e);
+    default: return rank_fn_j<16>(pw, c, r, e);
   }
 }
 
@@ -727,9 +741,10 @@ int32_t tree_rank_layout(const taccl_plan &p, TreeArgs &a) {
   const int32_t pw = rank_words(P);
   // Any rank count up to 32 and any route length (entering links come from a
   // table per vertex and option): wherever both fit, this kernel took 0.11 to
-  // 0.43 of the general kernel's time (9999 candidates on three 8-rank
+  // 0.45 of the general kernel's time (9999 candidates on three 8-rank
   // meshes 342 -> 106 us, 4000 on a 30-rank ring 511 -> 117 us, 20000
-  // Allreduces on 14 ranks 889 -> 378 us). Past 512 slots only chunks of 9 ranks or
+  // Allreduces on 14 ranks 889 -> 378 us, 4000 broadcasts of 8 chunks on 32
+  // ranks, 3 options, 62.9 -> 28.3 us). Past 512 slots only chunks of 9 ranks or
   // more (3 route words) are instantiated; staged route words and a slot's
   // word base bound the chunks (256 words).
   if (p.coll.kind == TACCL_ALLTOALL || p.topt.empty() || p.tent.empty() || p.pq_range <= 0 ||
@@ -786,11 +801,8 @@ int32_t tree_rank_layout(const taccl_plan &p, TreeArgs &a) {
   // mod 32 (two owners' rows fall on different bank halves)
   a.opt_ostride = pw * V + ((16 - (pw * V) % 32) + 32) % 32;
   a.o_opt = take(4 * P * a.opt_ostride);
-  a.o_ent = off;
-  if (CV <= 512) take(P * V * P * K);  // larger plans read it from global memory
   a.o_slot = take(8 * CV);
   if ((int64_t)P * V * P * K >= (1 << 20)) return 0;  // entering-link base: 20 bits
-  a.o_wave = off;
   const int32_t S = std::max<int64_t>(std::min<int64_t>(p.max_sends, CV), 1);
   int r = 0;
   while ((1 << r) < V) r++;
@@ -824,6 +836,22 @@ int32_t tree_rank_layout(const taccl_plan &p, TreeArgs &a) {
   a.w_lst = w;
   w = align16(w + 4 * 65);
   a.wave_bytes = w;
+  // The entering links' place. Every block copies the table and it takes the
+  // LDS of wavefronts, so past 8 ranks it is read from global memory (the L2
+  // holds it) unless it is small and a block of 12 wavefronts fits beside it
+  // where registers admit no more than those: 4000 broadcasts of 16 chunks on
+  // 32 ranks, 3 options (98 KB, 2 wavefronts per CU in LDS), 277 us in LDS and
+  // 56 us so; 24 ranks, 4 options (55 KB) 35.9 and 32.0 us; 20000 Allgathers
+  // on two nodes of 8 ranks, one chunk a rank (256 slots: the registers admit
+  // 20), 82 and 71 us; but 124 and 125 us with two chunks a rank, and 9000 on
+  // two nodes of 9 50.8 and 58.0 us. Past 512 slots it is never in LDS.
+  const int32_t ent = P * V * P * K;
+  a.ent_lds = pw < 3 ? CV <= 512
+                     : CV > 256 && CV <= 512 && ent <= kRankEntLds &&
+                           off + align16(ent) + 12 * a.wave_bytes <= kLdsBytes;
+  a.o_ent = off;
+  if (a.ent_lds) take(ent);
+  a.o_wave = off;
   return a.o_wave + a.wave_bytes;
 }
 
@@ -852,7 +880,7 @@ std::vector<uint8_t> tree_rank_image(const taccl_plan &p) {
       for (int32_t d = 0; d < P; d++)
         opt[4 * (o * a.opt_ostride + d / 4 * V + v) + d % 4] = 
             p.topt[((size_t)o * V + v) * p.topt_stride + d];
-  if (C * V <= 512) std::copy(p.tent.begin(), p.tent.begin() + P * V * P * K, b + a.o_ent);
+  if (a.ent_lds) std::copy(p.tent.begin(), p.tent.begin() + P * V * P * K, b + a.o_ent);
   uint32_t *slot = (uint32_t *)(b + a.o_slot);
   for (int32_t c = 0; c < C; c++)
     for (int32_t v = 0; v < V; v++) {

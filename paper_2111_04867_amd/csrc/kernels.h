@@ -217,6 +217,7 @@ constexpr int kTreeMaxThreads = 512;  // up to 8 wavefronts per block
 // would spill to scratch; larger plans run on the general kernel)
 constexpr int kLayerMaxSlotsPerLane = 8;
 constexpr int kRankMaxThreads = 768;  // ranked multicast kernel: up to 12
+constexpr int kRankEntLds = 20 * 1024;  // its largest entering-link table in LDS past 8 ranks
 constexpr int kRankMaxSlots = 1024;   // its (chunk, vertex) slots: 16 per lane
 constexpr int kRankMaxRange = 1 << 21;  // its codes of a path length (22 key bits hold two)
 constexpr int kTreeRecLdsMax = 32768;  // route records kept in LDS up to this size

@@ -36,15 +36,19 @@ inline int blocks_by_lds(int64_t bytes, int64_t lds_per_cu) {
 // contiguous Allgathers on two 8-rank meshes, 82.3 us with two blocks of 10
 // wavefronts, 64.8 us with two of 8; 20000 Allgathers on two nodes of 7
 // ranks, 182 us with three blocks of 4 (54528 bytes), 126 us with one of 12.
+// whole: a single block is taken before several that hold as many wavefronts
+// (the ranked kernel deals candidates out over the blocks then: the same
+// Allgathers 125 us with three blocks of 4, 114 us with one of 12).
 inline LaunchShape resident_shape(int64_t shared, int64_t wave, int max_waves, int per_simd,
-                                  int64_t max_lds = kLdsBytes, int64_t lds_per_cu = kLdsBytes) {
+                                  bool whole = false, int64_t max_lds = kLdsBytes,
+                                  int64_t lds_per_cu = kLdsBytes) {
   LaunchShape best{1, 1};
   int most = 0;
   for (int w = 1; w <= max_waves; w++) {
     const int64_t bytes = shared + w * wave;
     if (bytes > max_lds) break;
     const int n = std::min(blocks_by_lds(bytes, lds_per_cu), blocks_by_waves(w, per_simd));
-    if (n * w > most) {
+    if (n * w > most || (n * w == most && n == 1 && whole)) {
       most = n * w;
       best = LaunchShape{w, n};
     }

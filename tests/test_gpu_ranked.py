@@ -170,6 +170,38 @@ def test_greedy_slot_counts(P, C, order):
     check(order(broadcast(cf.full_ag(P, k=2) if P != 27 else ring(P), C)), n=33)
 
 
+@pytest.mark.parametrize("P,C,k", [(9, 5, 3), (12, 10, 2), (9, 28, 2), (16, 14, 3), (18, 18, 3),
+                                   (22, 15, 3), (24, 16, 8), (24, 21, 2), (31, 16, 2), (32, 16, 4),
+                                   (16, 32, 8), (14, 28, 4)])
+def test_entering_links(P, C, k):
+    """Entering links in global memory and in LDS, at every slots-per-lane
+    step up to 8 and every row width past 8 ranks."""
+    if P % 8 == 0 and P > 16:
+        w = broadcast(cf.cubemesh_nodes_ag(P // 8, k=k), C)
+    elif P == 16 and k == 8:
+        w = torus_broadcast(4, P, C, k)
+    else:
+        w = broadcast(cf.full_ag(P, k=k) if P * P <= 256 else ring(P, k=k), C)
+    from paper_2111_04867_amd.binding import Plan
+    assert Plan.from_workload(w).kernels == "tree_rank"
+    check(w, n=50)
+    if w.node_of is None:
+        w = replace(w, node_of=np.array([r * 2 // w.V for r in range(w.V)], dtype=np.int32))
+    check(cf.with_contiguity(w), n=50)
+
+
+# 12, 14 and 16 slots per lane at every row width, contiguous transfers too
+@pytest.mark.parametrize("P,C", [(12, 64), (12, 70), (16, 52), (24, 34), (16, 45), (22, 40),
+                                 (12, 85), (28, 30), (30, 32)])
+def test_slots_past_640(P, C):
+    from paper_2111_04867_amd.binding import Plan
+    w = broadcast(cf.full_ag(P, k=2) if P <= 16 else ring(P), C)
+    assert Plan.from_workload(w).kernels == "tree_rank"
+    check(w, n=33)
+    nodes = np.array([r * 2 // P for r in range(P)], dtype=np.int32)
+    check(cf.with_contiguity(replace(w, node_of=nodes)), n=33)
+
+
 def torus_broadcast(side, P, C, k):
     """C chunks to the first P of side x side torus vertices, the others
     switches: tables of P * P * side^2 * k bytes."""

@@ -58,6 +58,18 @@ def test_greedy_keeps_large_tables_out_of_lds(nodes, chunks, k, order):
     assert p.info["lds_bytes"] <= 48 * 1024
 
 
+# the same for the ranked kernel, its shared tables (43 KB at 32 ranks) and one
+# wavefront's state without the entering links
+@pytest.mark.parametrize("nodes,chunks,k", [(4, 16, 2), (4, 16, 3), (4, 16, 4), (4, 16, 8),
+                                            (4, 4, 3), (3, 20, 8), (3, 8, 4), (3, 21, 3)])
+@pytest.mark.parametrize("contiguity", [0, 1])
+def test_ranked_keeps_large_tables_out_of_lds(nodes, chunks, k, contiguity):
+    w = mesh_broadcast(nodes, chunks, k)
+    p = Plan.from_workload(cf.with_contiguity(w) if contiguity else w)
+    assert p.kernels == "tree_rank"
+    assert p.info["lds_bytes"] <= 58 * 1024
+
+
 @pytest.mark.parametrize("order", [lambda w: w, cf.with_greedy, cf.with_reverse_greedy,
                                    lambda w: cf.as_reduction(w, cf.ALLREDUCE)],
                          ids=["static", "greedy", "reverse", "allreduce"])
