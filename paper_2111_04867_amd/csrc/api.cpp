@@ -465,11 +465,18 @@ taccl_status_t taccl_connections_batch(taccl_plan_t p, int64_t n, const uint8_t 
     a.nwords = (a.C + 3) / 4;
     a.lanes = 4;
     while (a.lanes < 64 && a.lanes < a.nwords) a.lanes *= 2;
-    a.rec_lds = 4 * a.nrec <= kConnRecLdsMax;
     a.routes_words = (p->route_stride % 4 == 0) && (((uintptr_t)d_routes & 3) == 0);
+    const int64_t cus = std::max(t->num_cus, 1), per_wave = 64 / a.lanes;
+    // The record table is copied to LDS when a CU makes half as many lookups as
+    // it has records or more, or it is small; else it is read from the L2. 24
+    // ranks on a switch (12697 records, 576 lookups a candidate): 64 candidates 8.3
+    // us with the copy and 4.3 us without, 2000 (4500 lookups per CU) 7.0 and
+    // 5.3 us, 4000 7.1 and 7.9 us, 20000 12.2 and 18.8 us; 8 ranks (393
+    // records) 4.4 and 4.6 us at any batch.
+    a.rec_lds = 4 * a.nrec <= kConnRecLdsMax &&
+                (a.nrec <= kConnRecSmall || n * a.C / cus >= a.nrec / 2);
     // as many wavefronts per block as spread the batch over every CU, 4 at
     // least (they share the record table), 16 at most
-    const int64_t cus = std::max(t->num_cus, 1), per_wave = 64 / a.lanes;
     const int64_t want = (n + per_wave - 1) / per_wave;
     int waves = (int)std::min<int64_t>(kConnWaveThreads / 64, std::max<int64_t>(4, want / cus));
     while (waves > 1 && connections_wave_lds_bytes(a, waves) > t->max_lds) waves--;

@@ -208,8 +208,10 @@ inline int rank_words(int P) {
 
 constexpr int kConnMaxThreads = 256;
 constexpr int kConnWaveThreads = 1024;
-// record tables up to this size are copied to LDS by every block
+// record tables up to this size may be copied to LDS by every block, and
+// those of up to this many records always are
 constexpr int kConnRecLdsMax = 64 * 1024;
+constexpr int kConnRecSmall = 2048;
 
 constexpr int kTreeMaxThreads = 512;  // up to 8 wavefronts per block
 // (chunk, vertex) slots per lane of the layered and greedy multicast

@@ -149,6 +149,12 @@ def many_options(P, k):
     (many_options(16, 120), 33),   # record table beyond LDS, one word per lane
     (star(64, cf.ALLTOALL, relays=False), 40),  # largest byte matrix
     (star(65, cf.ALLTOALL, relays=False), 9),   # past it
+    # record tables of 2000 to 16000 records: batches on either side of the
+    # one from which they are copied to LDS, words of rows and odd rows
+    (star(14, cf.ALLTOALL), 1500), (star(14, cf.ALLTOALL), 2700),
+    (star(16, cf.ALLTOALL), 1799), (star(16, cf.ALLTOALL), 1801),
+    (star(17, cf.ALLTOALL), 2900), (star(20, cf.ALLTOALL, cpr=2), 1800),
+    (star(24, cf.ALLTOALL), 3), (star(64, cf.ALLTOALL, relays=False), 200),
 ], ids=lambda x: x.name if hasattr(x, "name") else str(x))
 def test_alltoall_variants(w, n):
     check(w, n, 3 + n, unrouted=0.05)
