@@ -32,7 +32,8 @@
 // What bounds it: the windows (268 on fournode64), in which every chunk's
 // next hop is looked at for about 60 that go: vector issue, and the LDS
 // atomics, which queue when lanes of a wavefront share a link. Hence the
-// diagonal thread order (below) and one straight line for all slots:
+// diagonal thread order where links are shared (the plan builder's rule) and
+// one straight line for all slots:
 // fournode64, 8192 candidates, 12.15 ms with chunks in index order (64 lanes
 // on one uplink), 10.08 ms along the diagonals, 9.38 ms without the branches
 // around chunks that are through.
@@ -66,7 +67,8 @@ constexpr int greedy_block_min_waves() {
 }
 
 // kStaged: the candidate's priorities are staged in LDS (a.b_sprio >= 0)
-template <int CPT, int NT, bool kPack, bool kStaged>
+// kDiag: thread order of the chunks (both in one kernel cost 1 to 3%)
+template <int CPT, int NT, bool kPack, bool kStaged, bool kDiag>
 __global__ __launch_bounds__(NT) __attribute__((
     amdgpu_waves_per_eu(greedy_block_min_waves<CPT, kPack>(), 8))) void path_greedy_block(PathGreedyArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
@@ -124,16 +126,27 @@ __global__ __launch_bounds__(NT) __attribute__((
       qo[j] = 0;
       hc[j] = 0;
       if (n < (uint32_t)a.C) {
-        // thread order runs along the diagonals of the (source, destination)
-        // matrix: the chunks of one wavefront have different sources and
-        // different destinations, so their first and last hops (and mostly
-        // those between) are on different links and the windows' atomic
-        // minima do not queue on one word
-        const uint32_t k0 = P > 1 ? __umulhi(n, a.pmagic) : n, s = n - k0 * P;
-        const uint32_t jj = P > 1 ? __umulhi(k0, a.pmagic) : k0;
-        uint32_t d = s + (k0 - jj * P);
-        d = d >= (uint32_t)P ? d - P : d;
-        const uint32_t sd = s * P + d, c = sd * (uint32_t)a.cpr + jj;
+        // kDiag: thread order runs along the diagonals of the (source,
+        // destination) matrix: the chunks of one wavefront have different
+        // sources and different destinations, so their first and last hops
+        // (and mostly those between) are on different links and the windows'
+        // atomic minima do not queue on one word. Otherwise chunks are in
+        // index order, which loads routes and priorities by whole lines
+        uint32_t s, d, sd, c;
+        if constexpr (kDiag) {
+          const uint32_t k0 = P > 1 ? __umulhi(n, a.pmagic) : n;
+          const uint32_t jj = P > 1 ? __umulhi(k0, a.pmagic) : k0;
+          s = n - k0 * P;
+          d = s + (k0 - jj * P);
+          d = d >= (uint32_t)P ? d - P : d;
+          sd = s * P + d;
+          c = sd * (uint32_t)a.cpr + jj;
+        } else {
+          sd = a.cpr > 1 ? __umulhi(n, a.cmagic) : n;  // n / cpr
+          s = P > 1 ? __umulhi(sd, a.pmagic) : sd;
+          d = sd - s * P;
+          c = n;
+        }
         hc[j] = c;
         if (s != d) {
           const uint32_t k = rt[c];
@@ -368,24 +381,32 @@ __global__ __launch_bounds__(NT) __attribute__((
   }
 }
 
-template <int NT, bool kPack, bool kStaged>
-const void *block_fn_ps(int cpt) {
+template <int NT, bool kPack, bool kStaged, bool kDiag>
+const void *block_fn_psd(int cpt) {
   switch (cpt) {
-    case 1: return (const void *)path_greedy_block<1, NT, kPack, kStaged>;
-    case 2: return (const void *)path_greedy_block<2, NT, kPack, kStaged>;
-    default: return (const void *)path_greedy_block<4, NT, kPack, kStaged>;
+    case 1: return (const void *)path_greedy_block<1, NT, kPack, kStaged, kDiag>;
+    case 2: return (const void *)path_greedy_block<2, NT, kPack, kStaged, kDiag>;
+    default: return (const void *)path_greedy_block<4, NT, kPack, kStaged, kDiag>;
   }
 }
 
+template <int NT, bool kPack, bool kStaged>
+const void *block_fn_ps(int cpt, bool diag) {
+  return diag ? block_fn_psd<NT, kPack, kStaged, true>(cpt)
+              : block_fn_psd<NT, kPack, kStaged, false>(cpt);
+}
+
 template <int NT, bool kPack>
-const void *block_fn_p(int cpt, bool staged) {
-  return staged ? block_fn_ps<NT, kPack, true>(cpt) : block_fn_ps<NT, kPack, false>(cpt);
+const void *block_fn_p(int cpt, bool staged, bool diag) {
+  return staged ? block_fn_ps<NT, kPack, true>(cpt, diag)
+                : block_fn_ps<NT, kPack, false>(cpt, diag);
 }
 
 template <int NT>
 const void *block_fn(const PathGreedyArgs &a) {
   const bool staged = a.b_sprio >= 0;
-  return a.pack ? block_fn_p<NT, true>(a.cpt, staged) : block_fn_p<NT, false>(a.cpt, staged);
+  return a.pack ? block_fn_p<NT, true>(a.cpt, staged, a.diagonal != 0)
+                : block_fn_p<NT, false>(a.cpt, staged, a.diagonal != 0);
 }
 
 int bits_for(uint64_t x) {  // bits to hold values 0..x
@@ -411,6 +432,9 @@ int32_t path_greedy_block_layout(const taccl_plan &p, PathGreedyArgs &a) {
   a.nslots = C * H;
   // x / P = umulhi(x, pmagic) for x below 2^16 and P > 1
   a.pmagic = p.topo.P > 1 ? (uint32_t)((1ull << 32) / p.topo.P + 1) : 0u;
+  const uint32_t cpr = (uint32_t)std::max(p.coll.cpr, 1);
+  a.cmagic = cpr > 1 ? (uint32_t)((1ull << 32) / cpr + 1) : 0u;
+  a.diagonal = p.gk_diagonal;
   a.cpt = cpt;
   // one-word keys: a relative start below 2 c_min + c_max must stay below
   // the clamp value 2^rb - 1

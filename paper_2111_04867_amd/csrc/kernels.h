@@ -163,7 +163,8 @@ struct PathGreedyArgs {
   // block-per-candidate variant for larger plans: Step-2 key rank of every
   // hop (plan table), chunks per thread and the LDS carve-up
   const uint32_t *gkrank;
-  uint32_t pmagic;
+  uint32_t pmagic, cmagic;
+  int32_t diagonal;  // thread order of the chunks
   int32_t cpt, block_bytes;
   int32_t b_cost, b_lfree, b_best1, b_best2, b_lserv, b_lnext, b_red, b_fpos, b_sprio;
   // one-word window keys: start - previous window start (clamped to

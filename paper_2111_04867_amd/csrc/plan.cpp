@@ -472,6 +472,25 @@ static taccl_status_t build_levels(taccl_plan *p) {
     for (size_t j = 0; j < keys.size(); j++)
       p->gkrank[j] = (uint32_t)(std::lower_bound(uniq.begin(), uniq.end(), keys[j]) - uniq.begin());
     p->gk_count = (int32_t)uniq.size();
+    // Thread order of the block kernel. In index order a wavefront's chunks
+    // have one source, so where a source's routes start on few links (behind a
+    // switch) the windows' minima queue on those; along the diagonals they
+    // don't, but their routes and priorities are loaded a line each. 2000
+    // candidates, index order and diagonals: 23 ranks on a switch, 3 chunks a
+    // pair, 1008 and 787 us; 27 fully connected ranks, 2 chunks, 84 and 95 us.
+    // In reverse path order the first hop served is the last one, which
+    // chunks of one source never share: 1551 and 1641 us, 138 and 154 us; only
+    // with the longer routes between switches (5 hops; four of 16 ranks 4962
+    // and 4834 us) do the diagonals gain.
+    std::vector<uint8_t> seen((size_t)E, 0);
+    int64_t first_links = 0;  // links that some route starts on
+    for (size_t q = 0; q < npath; q++)
+      if (p->path_off[q + 1] > p->path_off[q]) {
+        uint8_t &x = seen[p->path_links[p->path_off[q]]];
+        first_links += !x;
+        x = 1;
+      }
+    p->gk_diagonal = p->greedy == 2 ? p->H >= 5 : 2 * first_links < (int64_t)P * (P - 1);
   }
 
   const int32_t C = p->coll.C, cpr = p->coll.cpr;

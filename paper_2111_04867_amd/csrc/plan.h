@@ -197,6 +197,7 @@ struct taccl_plan {
   // order), and the number of distinct ranks
   std::vector<uint32_t> gkrank;
   int32_t gk_count = 0;
+  bool gk_diagonal = false;  // the block kernel's thread order of the chunks
 
   // connection count of Alltoall plans whose routes form at most two
   // switched rank pairs each: per route option (option q at record q + 1,

@@ -262,3 +262,30 @@ def test_reverse_path_order_differs_from_path_order():
     m1, _ = check(fwd[0], fwd[1], routes, prio, "twonode16 path order")
     m2, _ = check(rev[0], rev[1], routes, prio, "twonode16 reverse path order")
     assert (m1 != m2).any()
+
+
+def one_switch_a2a(P, cpr):
+    row_ptr, col, a, b = cf.csr_from_edges(P + 1, cf.switch_edges(range(P), P, 700, 8))
+    return cf.Workload(f"switch{P}x{cpr}_a2a", P + 1, P, row_ptr, col, a, b, None, cf.ALLTOALL, cpr,
+                       65536, cf.RELAY1)
+
+
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("make", [lambda: cf.full_a2a(19), lambda: replace(cf.full_a2a(23),
+                                                                          chunks_per_rank=2),
+                                  lambda: replace(cf.full_a2a(13), chunks_per_rank=7),
+                                  lambda: one_switch_a2a(17, 1), lambda: one_switch_a2a(19, 3),
+                                  lambda: one_switch_a2a(11, 9)],
+                         ids=["full19", "full23x2", "full13x7", "switch17", "switch19x3",
+                              "switch11x9"])
+def test_alltoall_block_thread_orders(make, order):
+    """The block kernel's two thread orders of the chunks (index order on full
+    meshes and in reverse path order, diagonals behind a switch), one or
+    several chunks per pair and per thread."""
+    w = replace(make(), order=order)
+    plan, ref, opts = plans(w)
+    assert plan.kernels == "path_greedy_block"
+    routes, prio = generate(17, 0, 9, opts, plan.prio_stride)
+    prio[::2] &= 7
+    routes[3, ::5] = 0xFF  # some chunks unrouted
+    check(plan, ref, routes, prio, f"{w.name} order={order}")
