@@ -137,11 +137,11 @@ LaunchShape wave_shape(taccl_plan *p, DeviceTables *t, Kernel kernel, bool reduc
   return s;
 }
 
-// The same for a kernel of one block size: its resident blocks per CU.
-LaunchShape block_shape(taccl_plan *p, DeviceTables *t, Kernel kernel, const void *fn, int threads,
-                        int bytes) {
+// The same for one block size of a kernel: its resident blocks per CU.
+LaunchShape block_shape(taccl_plan *p, DeviceTables *t, Kernel kernel, int variant, const void *fn,
+                        int threads, int bytes) {
   std::lock_guard<std::mutex> lock(p->mu);
-  LaunchShape &s = t->shape[kernel][0];
+  LaunchShape &s = t->shape[kernel][variant];
   if (!s.waves)
     s = LaunchShape{1, std::max(1, std::min(blocks_by_lds(bytes, t->lds_per_cu),
                                             blocks_by_registers(fn, threads, 1)))};
@@ -222,8 +222,8 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     g.n = n;
     if (kernel == kPathGreedyBlock) {
       // the block kernel has one size: only its resident blocks are asked for
-      const LaunchShape sh = block_shape(p, t, kernel, path_greedy_block_fn(g), kGreedyBlockThreads,
-                                         g.block_bytes);
+      const LaunchShape sh = block_shape(p, t, kernel, 0, path_greedy_block_fn(g),
+                                         kGreedyBlockThreads, g.block_bytes);
       const int bgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
       e = launch_path_greedy_block(g, bgrid, s);
       if (e != hipSuccess) return hip_fail(e, "kernel launch");
@@ -257,7 +257,9 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     pa.makespan = d_makespan;
     pa.valid = d_valid;
     pa.n = n;
-    const LaunchShape sh = block_shape(p, t, kernel, path_ports_fn(pa), pa.nt, pa.lds_bytes);
+    path_ports_block(pa, n, t->num_cus);
+    const LaunchShape sh =
+        block_shape(p, t, kernel, pa.nt / 512, path_ports_fn(pa), pa.nt, pa.lds_bytes);
     const int pgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
     e = launch_path_ports(pa, pgrid, s);
   } else if (p->coll.kind == TACCL_ALLTOALL) {
@@ -306,7 +308,7 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
     if (kernel == kPathFast) {
       const int cpt = path_fast_cpt(*p), nt = path_fast_threads(*p);
       const LaunchShape sh =
-          block_shape(p, t, kernel, path_fast_fn(a, cpt, nt), nt, a.lds_bytes);
+          block_shape(p, t, kernel, 0, path_fast_fn(a, cpt, nt), nt, a.lds_bytes);
       const int fgrid = (int)std::min<int64_t>(n, (int64_t)std::max(t->num_cus, 1) * sh.per_cu);
       e = launch_path_fast(a, cpt, nt, fgrid, s);
     } else {

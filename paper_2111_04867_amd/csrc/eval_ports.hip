@@ -341,12 +341,14 @@ __global__ __launch_bounds__(NT) void path_eval_ports(PortsArgs a) {
 }
 
 const void *ports_fn(int cpt, int nt) {
-  if (nt == 256) return (const void *)path_eval_ports<1, 256>;
-  if (nt == 512) return (const void *)path_eval_ports<1, 512>;
-  switch (cpt) {
-    case 1: return (const void *)path_eval_ports<1, 1024>;
-    case 2: return (const void *)path_eval_ports<2, 1024>;
-    case 4: return (const void *)path_eval_ports<4, 1024>;
+  switch (nt * 8 + cpt) {
+    case 256 * 8 + 1: return (const void *)path_eval_ports<1, 256>;
+    case 256 * 8 + 4: return (const void *)path_eval_ports<4, 256>;
+    case 512 * 8 + 1: return (const void *)path_eval_ports<1, 512>;
+    case 512 * 8 + 2: return (const void *)path_eval_ports<2, 512>;
+    case 1024 * 8 + 1: return (const void *)path_eval_ports<1, 1024>;
+    case 1024 * 8 + 2: return (const void *)path_eval_ports<2, 1024>;
+    case 1024 * 8 + 4: return (const void *)path_eval_ports<4, 1024>;
   }
   return nullptr;
 }
@@ -391,6 +393,20 @@ int32_t path_ports_layout(const taccl_plan &p, PortsArgs &a) {
   a.o_red = take(4 * 2 * (1024 / 64));
   a.lds_bytes = off;
   return off;
+}
+
+// One candidate per block, and its walk keeps a few wavefronts busy, so with
+// 513 to 1024 chunks a batch that fills the CUs takes smaller blocks, of which
+// a CU holds more (registers admit one of 1024 threads, two of 512, four of
+// 256), as far as a thread per send port goes. 24 ranks on two switches: 3000
+// candidates 281 us in blocks of 1024 (261 on the general kernel, whose
+// blocks have 256), 165 of 512, 111 of 256; 300 candidates 49.8, 30.7 and
+// 34.9 us; one 24.7, 25.7 and 30.3 us.
+void path_ports_block(PortsArgs &a, int64_t n, int cus) {
+  if (a.C <= 512 || a.C > 1024) return;
+  a.nt = n <= cus ? 1024 : n <= 2 * (int64_t)cus ? 512 : 256;
+  while (a.nt < a.nports) a.nt *= 2;
+  a.cpt = 1024 / a.nt;
 }
 
 const void *path_ports_fn(const PortsArgs &a) { return ports_fn(a.cpt, a.nt); }

@@ -275,6 +275,8 @@ bool path_ports_supported(const taccl_plan &p, int max_lds);
 // Alltoall with switch ports: fills the layout and returns the block's LDS
 // bytes, or 0 when the plan does not meet the kernel's conditions
 int32_t path_ports_layout(const taccl_plan &p, PortsArgs &a);
+// block size for a batch of n candidates, of those that the layout allows
+void path_ports_block(PortsArgs &a, int64_t n, int cus);
 const void *path_ports_fn(const PortsArgs &a);
 hipError_t launch_path_ports(const PortsArgs &a, int grid, hipStream_t stream);
 

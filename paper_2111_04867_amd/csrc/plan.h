@@ -83,7 +83,9 @@ struct DeviceTables {
   // Depends on the plan and the device alone, so it is worked out on first
   // use and kept (under the plan's mutex): the runtime's occupancy query for
   // every block size cost 2-3 us on each call (one query now, on the first)
-  LaunchShape shape[kNumKernels][2];  // [1]: the ReduceScatter variant
+  // [1]: the ReduceScatter variant; Alltoall with switch ports: 256, 512 and
+  // 1024 threads
+  LaunchShape shape[kNumKernels][3];
   int max_lds = 0;  // bytes of LDS a block may use on this device
   int lds_per_cu = 0;
   int num_cus = 0;

@@ -168,6 +168,36 @@ def test_block_sizes(P, cpr, n):
         check(plan, ref, routes, prio, f"{w.name} cpr={cpr}")
 
 
+def switch_and_mesh(P):
+    """A switch next to direct links between every two ranks: more send ports
+    than a small block has threads."""
+    edges = cf.switch_edges(range(P), P, 700, 8)
+    edges += [(u, v, 1300, 20) for u in range(P) for v in range(P) if u != v]
+    row_ptr, col, a, b = cf.csr_from_edges(P + 1, edges)
+    return cf.Workload(f"switchmesh{P}", P + 1, P, row_ptr, col, a, b, None, cf.ALLTOALL, 1, 65536,
+                       cf.KSHORTEST, k=2, switch_ports=1)
+
+
+# 513 to 1024 chunks: blocks of 1024 threads up to 256 candidates, 512 up to
+# 512, then 256, or as many as there are send ports
+@pytest.mark.parametrize("make", [lambda: star(23, relays=True, cpr=1),
+                                  lambda: star(32, relays=False, cpr=1),
+                                  lambda: star(13, relays=True, cpr=6),
+                                  lambda: switch_and_ring(27, 1), lambda: switch_and_mesh(24),
+                                  lambda: switch_and_mesh(30)],
+                         ids=["star23", "star32", "star13x6", "ring27", "mesh24", "mesh30"])
+@pytest.mark.parametrize("n", [256, 257, 512, 513, 1100])
+def test_block_size_by_batch(make, n):
+    w = make()
+    plan, ref, opts = plans(w)
+    assert plan.kernels == "path_eval_ports"
+    routes, prio = generate(9, 0, n, opts, plan.prio_stride)
+    rng = np.random.default_rng(n)
+    routes[rng.random(routes.shape) < 0.01] = 0xFF
+    prio[rng.random(prio.shape) < 0.3] &= 1
+    check(plan, ref, routes, prio, f"{w.name} n={n}")
+
+
 def test_unaligned_routes():
     """Route rows of whole words behind a pointer that is not word aligned."""
     w = star(16, True, 1)
