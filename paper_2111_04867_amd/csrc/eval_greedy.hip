@@ -132,21 +132,13 @@ __global__ __launch_bounds__(NT) __attribute__((
         // (and mostly those between) are on different links and the windows'
         // atomic minima do not queue on one word. Otherwise chunks are in
         // index order, which loads routes and priorities by whole lines
-        uint32_t s, d, sd, c;
-        if constexpr (kDiag) {
-          const uint32_t k0 = P > 1 ? __umulhi(n, a.pmagic) : n;
-          const uint32_t jj = P > 1 ? __umulhi(k0, a.pmagic) : k0;
-          s = n - k0 * P;
-          d = s + (k0 - jj * P);
-          d = d >= (uint32_t)P ? d - P : d;
-          sd = s * P + d;
-          c = sd * (uint32_t)a.cpr + jj;
-        } else {
-          sd = a.cpr > 1 ? __umulhi(n, a.cmagic) : n;  // n / cpr
-          s = P > 1 ? __umulhi(sd, a.pmagic) : sd;
-          d = sd - s * P;
-          c = n;
-        }
+        const uint32_t k0 = kDiag ? (P > 1 ? __umulhi(n, a.pmagic) : n)
+                                  : (a.cpr > 1 ? __umulhi(n, a.cmagic) : n),  // n / cpr
+                       s = kDiag ? n - k0 * P : (P > 1 ? __umulhi(k0, a.pmagic) : k0);
+        const uint32_t jj = kDiag ? (P > 1 ? __umulhi(k0, a.pmagic) : k0) : 0u;
+        uint32_t d = kDiag ? s + (k0 - jj * P) : k0 - s * P;
+        if (kDiag) d = d >= (uint32_t)P ? d - P : d;
+        const uint32_t sd = kDiag ? s * P + d : k0, c = kDiag ? sd * (uint32_t)a.cpr + jj : n;
         hc[j] = c;
         if (s != d) {
           const uint32_t k = rt[c];
