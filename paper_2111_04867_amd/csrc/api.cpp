@@ -124,8 +124,7 @@ int blocks_by_registers(const void *fn, int threads, int otherwise) {
 }
 
 // The launch shape of a kernel whose blocks hold wavefronts of `wave` bytes
-// of LDS beside `shared` bytes, up to max_waves of them. fn null: a kernel
-// whose registers don't bound it.
+// of LDS beside `shared` bytes, up to max_waves of them.
 LaunchShape wave_shape(taccl_plan *p, DeviceTables *t, Kernel kernel, bool reduce, const void *fn,
                        int shared, int wave, int max_waves) {
   std::lock_guard<std::mutex> lock(p->mu);
@@ -133,7 +132,7 @@ LaunchShape wave_shape(taccl_plan *p, DeviceTables *t, Kernel kernel, bool reduc
   if (!s.waves)
     // a block of four wavefronts has one on every SIMD
     s = resident_shape(shared, wave, max_waves, std::min(blocks_by_registers(fn, 256, 8), 8),
-                       kernel == kTreeRank, t->max_lds, t->lds_per_cu);
+                       kernel == kTreeRank || kernel == kTree, t->max_lds, t->lds_per_cu);
   return s;
 }
 
@@ -370,19 +369,20 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
       const void *fn = k == kTreeRank     ? tree_rank_fn(y)
                        : k == kTreeGreedy ? tree_greedy_fn(y)
                        : k == kTreeLayers ? tree_layers_fn(y)
-                                          : nullptr;
+                                          : tree_fn(y);
       const LaunchShape sh =
           wave_shape(p, t, k, y.reduce != 0, fn, y.o_wave, y.wave_bytes,
                      k == kTreeRank ? tree_rank_max_waves(y) : kTreeMaxThreads / 64);
       y.waves_per_block = sh.waves;
-      // The ranked kernel's candidates are dealt out over the blocks where a CU
-      // holds one of them, so that a batch which is no multiple of the resident
-      // wavefronts leaves every CU with as few as it can (20000 Allgathers on
-      // two 8-rank meshes 144 -> 129 us, 44 Allreduces on two nodes of 7 ranks
-      // 41.1 -> 30.4 us). With several blocks per CU they fill up block by
-      // block: dealt out, the last ones would all be on the SIMDs of the
-      // blocks' first wavefronts (20000 Allgathers on 10 ranks 35.1 -> 38.2 us).
-      const bool spread = k == kTreeRank && sh.per_cu == 1;
+      // Candidates are dealt out over the blocks where a CU holds one of them,
+      // so that a batch which is no multiple of the resident wavefronts leaves
+      // every CU with as few as it can (20000 Allgathers on two 8-rank meshes
+      // 144 -> 129 us, 44 Allreduces on two nodes of 7 ranks 41.1 -> 30.4 us),
+      // and where there is a CU for each candidate. Else several blocks per
+      // CU fill up block by block: dealt out, the last candidates would all be
+      // on the SIMDs of the blocks' first wavefronts (20000 Allgathers on 10
+      // ranks 35.1 -> 38.2 us).
+      const bool spread = sh.per_cu == 1 || n <= t->num_cus;
       const int tgrid = wave_grid(sh, n, t->num_cus, spread);
       y.first_block = spread ? 1 : sh.waves;
       y.first_wave = spread ? tgrid : 1;

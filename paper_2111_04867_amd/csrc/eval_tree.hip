@@ -461,7 +461,7 @@ __global__ __launch_bounds__(kTreeMaxThreads) void tree_eval_kernel(TreeArgs a) 
   uint32_t *gst = (uint32_t *)(wl + a.w_gst), *grem = gst + E, *gcnt = grem + E, *gfirst = gcnt + E;
 
   const int64_t stride = (int64_t)gridDim.x * a.waves_per_block;
-  const int64_t first = (int64_t)blockIdx.x * a.waves_per_block + wave;
+  const int64_t first = blockIdx.x * a.first_block + wave * a.first_wave;
   // Software pipeline: the next candidate's routes and priorities are
   // loaded into registers while the current one is evaluated, so the HBM
   // latency overlaps the work instead of stalling every candidate.
@@ -975,7 +975,7 @@ void tree_layers_kernel(TreeArgs a) {
   };
 
   const int64_t stride = (int64_t)gridDim.x * a.waves_per_block;
-  const int64_t first = (int64_t)blockIdx.x * a.waves_per_block + wave;
+  const int64_t first = blockIdx.x * a.first_block + wave * a.first_wave;
   const int nrw = a.route_stride >> 2;
   uint32_t pf_r[kPfRoute], pf_p[J];
   // the next candidate's routes and priorities stream into registers while
@@ -1621,7 +1621,7 @@ __global__ __launch_bounds__(kTreeMaxThreads) void tree_greedy_kernel(TreeArgs a
   uint32_t *gofs = (uint32_t *)(wl + a.w_gofs);  // [E + 1] first list entry per link
 
   const int64_t stride = (int64_t)gridDim.x * a.waves_per_block;
-  const int64_t first = (int64_t)blockIdx.x * a.waves_per_block + wave;
+  const int64_t first = blockIdx.x * a.first_block + wave * a.first_wave;
   // A chunk's row of P route bytes takes PW words (loaded from any byte
   // address; those that would pass the candidate's row are read from its
   // last four bytes and shifted down when staged)
@@ -1847,27 +1847,22 @@ int32_t tree_any_layout(const taccl_plan &p, TreeArgs &a) {
 int32_t tree_block_bytes(const TreeArgs &a, int waves) { return a.o_wave + waves * a.wave_bytes; }
 
 template <bool kAny>
-static void launch_tree_v(const TreeArgs &a, int grid, hipStream_t stream) {
+static const void *tree_fn_v(const TreeArgs &a) {
   const bool pf = a.routes_word_aligned && a.route_stride <= 4 * 64 * kPfRoute &&
                   a.C * a.V <= 64 * kPfPrio;
-  const dim3 g(grid), b(64 * a.waves_per_block);
-  const int bytes = tree_block_bytes(a, a.waves_per_block);
-  if (a.rec_in_lds && pf)
-    hipLaunchKernelGGL((tree_eval_kernel<true, true, kAny>), g, b, bytes, stream, a);
-  else if (a.rec_in_lds)
-    hipLaunchKernelGGL((tree_eval_kernel<true, false, kAny>), g, b, bytes, stream, a);
-  else if (pf)
-    hipLaunchKernelGGL((tree_eval_kernel<false, true, kAny>), g, b, bytes, stream, a);
-  else
-    hipLaunchKernelGGL((tree_eval_kernel<false, false, kAny>), g, b, bytes, stream, a);
+  if (a.rec_in_lds)
+    return pf ? (const void *)tree_eval_kernel<true, true, kAny>
+              : (const void *)tree_eval_kernel<true, false, kAny>;
+  return pf ? (const void *)tree_eval_kernel<false, true, kAny>
+            : (const void *)tree_eval_kernel<false, false, kAny>;
 }
 
+const void *tree_fn(const TreeArgs &a) { return a.any ? tree_fn_v<true>(a) : tree_fn_v<false>(a); }
+
 hipError_t launch_tree(const TreeArgs &a, int grid, hipStream_t stream) {
-  if (a.any)
-    launch_tree_v<true>(a, grid, stream);
-  else
-    launch_tree_v<false>(a, grid, stream);
-  return hipGetLastError();
+  void *args[] = {(void *)&a};
+  return hipLaunchKernel(tree_fn(a), dim3(grid), dim3(64 * a.waves_per_block), args,
+                         tree_block_bytes(a, a.waves_per_block), stream);
 }
 
 // ancestor doubling: 2^rounds >= V covers the deepest tree (V - 1 links)

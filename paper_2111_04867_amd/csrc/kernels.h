@@ -69,7 +69,7 @@ struct TreeArgs {
   const uint4 *rank_img;  // the block's shared LDS below o_wave, ready to copy
   const uint8_t *ent;
   // first candidate of a wavefront: first_block per block + first_wave per
-  // wavefront of the block (ranked kernel)
+  // wavefront of the block
   uint32_t first_block, first_wave;
   int32_t ent_lds;  // the entering-link table is in LDS
   int32_t o_rcost, o_ent, w_h, o_slot, opt_ostride, w_pj;
@@ -280,6 +280,7 @@ void path_ports_block(PortsArgs &a, int64_t n, int cus);
 const void *path_ports_fn(const PortsArgs &a);
 hipError_t launch_path_ports(const PortsArgs &a, int grid, hipStream_t stream);
 
+const void *tree_fn(const TreeArgs &a);
 hipError_t launch_tree(const TreeArgs &a, int grid, hipStream_t stream);
 // Alltoall greedy: fills the layout; returns the bytes of a one-wavefront
 // block, or 0 when the plan has more than 1024 send slots or 256 links
