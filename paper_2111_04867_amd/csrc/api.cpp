@@ -374,15 +374,16 @@ taccl_status_t taccl_eval_batch(taccl_plan_t p, int64_t n, const uint8_t *d_rout
           wave_shape(p, t, k, y.reduce != 0, fn, y.o_wave, y.wave_bytes,
                      k == kTreeRank ? tree_rank_max_waves(y) : kTreeMaxThreads / 64);
       y.waves_per_block = sh.waves;
-      // Candidates are dealt out over the blocks where a CU holds one of them,
-      // so that a batch which is no multiple of the resident wavefronts leaves
-      // every CU with as few as it can (20000 Allgathers on two 8-rank meshes
-      // 144 -> 129 us, 44 Allreduces on two nodes of 7 ranks 41.1 -> 30.4 us),
-      // and where there is a CU for each candidate. Else several blocks per
-      // CU fill up block by block: dealt out, the last candidates would all be
-      // on the SIMDs of the blocks' first wavefronts (20000 Allgathers on 10
-      // ranks 35.1 -> 38.2 us).
-      const bool spread = sh.per_cu == 1 || n <= t->num_cus;
+      // The ranked and the general kernel deal candidates out over the blocks
+      // where a CU holds one of them, so that a batch which is no multiple of
+      // the resident wavefronts leaves every CU with as few as it can (20000
+      // Allgathers on two 8-rank meshes 144 -> 129 us, 44 Allreduces on two
+      // nodes of 7 ranks 41.1 -> 30.4 us), and where there is a CU for each
+      // candidate. Else several blocks per CU fill up block by block: dealt
+      // out, the last candidates would all be on the SIMDs of the blocks' first
+      // wavefronts (20000 Allgathers on 10 ranks 35.1 -> 38.2 us).
+      const bool spread =
+          (k == kTreeRank || k == kTree) && (sh.per_cu == 1 || n <= t->num_cus);
       const int tgrid = wave_grid(sh, n, t->num_cus, spread);
       y.first_block = spread ? 1 : sh.waves;
       y.first_wave = spread ? tgrid : 1;

@@ -975,7 +975,7 @@ void tree_layers_kernel(TreeArgs a) {
   };
 
   const int64_t stride = (int64_t)gridDim.x * a.waves_per_block;
-  const int64_t first = blockIdx.x * a.first_block + wave * a.first_wave;
+  const int64_t first = (int64_t)blockIdx.x * a.waves_per_block + wave;
   const int nrw = a.route_stride >> 2;
   uint32_t pf_r[kPfRoute], pf_p[J];
   // the next candidate's routes and priorities stream into registers while
@@ -1621,7 +1621,7 @@ __global__ __launch_bounds__(kTreeMaxThreads) void tree_greedy_kernel(TreeArgs a
   uint32_t *gofs = (uint32_t *)(wl + a.w_gofs);  // [E + 1] first list entry per link
 
   const int64_t stride = (int64_t)gridDim.x * a.waves_per_block;
-  const int64_t first = blockIdx.x * a.first_block + wave * a.first_wave;
+  const int64_t first = (int64_t)blockIdx.x * a.waves_per_block + wave;
   // A chunk's row of P route bytes takes PW words (loaded from any byte
   // address; those that would pass the candidate's row are read from its
   // last four bytes and shifted down when staged)

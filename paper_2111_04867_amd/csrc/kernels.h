@@ -69,7 +69,7 @@ struct TreeArgs {
   const uint4 *rank_img;  // the block's shared LDS below o_wave, ready to copy
   const uint8_t *ent;
   // first candidate of a wavefront: first_block per block + first_wave per
-  // wavefront of the block
+  // wavefront of the block (ranked and general kernel)
   uint32_t first_block, first_wave;
   int32_t ent_lds;  // the entering-link table is in LDS
   int32_t o_rcost, o_ent, w_h, o_slot, opt_ostride, w_pj;
